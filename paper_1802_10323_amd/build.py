@@ -12,8 +12,12 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libpoisson_hip.so")
-SOURCES = [os.path.join(HERE, "csrc", name)
-           for name in ("poisson.hip", "r2r_async.hip", "r2r_async_wide.hip", "tri_async.hip")]
+LINE_PARTS = 8      # objects of r2r_line_part.hip, each with its share of the lengths
+# (source, extra flags, object name)
+UNITS = [(name, [], name + ".o")
+         for name in ("poisson.hip", "r2r_async.hip", "r2r_async_wide.hip", "tri_async.hip")]
+UNITS += [("r2r_line_part.hip", [f"-DPOISSON_LINE_PART_INDEX={i}"], f"r2r_line_part{i}.hip.o")
+          for i in range(LINE_PARTS)]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -41,11 +45,16 @@ def build(verbose=False):
     from concurrent.futures import ThreadPoolExecutor
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    objs = [os.path.join(objdir, os.path.basename(src) + ".o") for src in SOURCES]
+    objs = [os.path.join(objdir, obj) for _, _, obj in UNITS]
     compile_flags = [f for f in FLAGS if f != "-shared"]
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as pool:
-        list(pool.map(lambda so: _run([HIPCC, *compile_flags, "-c", so[0], "-o", so[1]], verbose),
-                      zip(SOURCES, objs)))
+
+    def compile_unit(unit):
+        src, extra, obj = unit
+        _run([HIPCC, *compile_flags, *extra, "-c", os.path.join(HERE, "csrc", src),
+              "-o", os.path.join(objdir, obj)], verbose)
+
+    with ThreadPoolExecutor(max_workers=min(len(UNITS), max(2, os.cpu_count() or 2))) as pool:
+        list(pool.map(compile_unit, UNITS))
     tmp = LIB + ".tmp"
     _run([HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", tmp], verbose)
     os.replace(tmp, LIB)

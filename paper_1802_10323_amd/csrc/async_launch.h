@@ -8,8 +8,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <map>
 #include <mutex>
-#include <vector>
+#include <utility>
 
 #include "r2r_fast.h"
 #include "tri_fast.h"
@@ -56,52 +57,26 @@ hipError_t async_wide_launch(const R2RFastArgs<double>& a, int kind, int inverse
 // the largest fields do.
 int grid_cap_blocks();
 
-// Blocks of a persistent launch of `fn` (512 threads, static LDS only): as
-// many as are resident at once, at most one per tile.
-inline int async_resident_blocks(const void* fn, long long ntiles) {
-  static std::mutex mu;
-  static std::vector<std::pair<std::pair<const void*, int>, int>> cache;   // (fn, device) -> blocks
-  int dev = 0;
-  (void)hipGetDevice(&dev);
-  int blocks = 0;
-  {
-    std::lock_guard<std::mutex> lk(mu);
-    for (auto& e : cache)
-      if (e.first.first == fn && e.first.second == dev) blocks = e.second;
-  }
-  if (!blocks) {
-    int cus = 0, per_cu = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 512, 0) != hipSuccess) per_cu = 1;
-    blocks = cus * std::max(per_cu, 1);
-    std::lock_guard<std::mutex> lk(mu);
-    cache.push_back({{fn, dev}, blocks});
-  }
-  const int cap = grid_cap_blocks();
-  if (cap > 0) blocks = std::min(blocks, cap);
-  return (int)std::min<long long>(ntiles, blocks);
-}
-
-// Blocks of a persistent launch of `fn` with 256 threads and static LDS
+// Blocks of a persistent launch of `fn` with `threads` threads and static LDS
 // only: as many as are resident at once (occupancy API), at most `work`.
-inline int direct_blocks(const void* fn, long long work) {
+inline int async_resident_blocks(const void* fn, long long work, int threads = 512) {
   static std::mutex mu;
-  static std::vector<std::pair<std::pair<const void*, int>, int>> cache;   // (fn, device) -> blocks
+  static std::map<std::pair<const void*, int>, int> cache;   // (fn, device) -> blocks
   int dev = 0;
   (void)hipGetDevice(&dev);
   int blocks = 0;
   {
     std::lock_guard<std::mutex> lk(mu);
-    for (auto& e : cache)
-      if (e.first.first == fn && e.first.second == dev) blocks = e.second;
+    const auto it = cache.find({fn, dev});
+    if (it != cache.end()) blocks = it->second;
   }
   if (!blocks) {
     int cus = 0, per_cu = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, 0) != hipSuccess) per_cu = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, 0) != hipSuccess) per_cu = 1;
     blocks = cus * std::max(per_cu, 1);
     std::lock_guard<std::mutex> lk(mu);
-    cache.push_back({{fn, dev}, blocks});
+    cache[{fn, dev}] = blocks;
   }
   const int cap = grid_cap_blocks();
   if (cap > 0) blocks = std::min(blocks, cap);

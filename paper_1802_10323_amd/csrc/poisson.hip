@@ -24,6 +24,7 @@
 #include "tri_fast.h"
 #include "batch_kernels.h"
 #include "async_launch.h"
+#include "line_launch.h"
 #include "refine_kernels.h"
 #include "projection.h"
 #include "navier_stokes.h"
@@ -425,15 +426,15 @@ static int resident_grid(const void* fn, int block, size_t lds, long long ntiles
 
 // ------------------------------------------------------------------ launches
 
-// Launch arguments of the size-specialised transform kernel (r2r_fast.h)
-// of configuration C.
-template <typename T, typename C>
-static R2RFastArgs<T> fast_args(const poisson_plan* p, const AxisTables& A, int inverse, T* data,
-                                const double* skip, double* out64 = nullptr) {
-  constexpr int M = C::M;
+// Launch arguments of the size-specialised transform kernels (r2r_fast.h,
+// r2r_line.h) of axis A with tiles of nl lines.
+template <typename T>
+static R2RFastArgs<T> fast_args(const poisson_plan* p, const AxisTables& A, int nl, int inverse,
+                                T* data, const double* skip, double* out64 = nullptr) {
+  const int M = A.m;
   R2RFastArgs<T> a{};
   a.data = data;
-  a.g = make_geom(A.axis, p->dims, ilog2(C::NL));
+  a.g = make_geom(A.axis, p->dims, ilog2(nl));
   a.kind = A.kind;
   a.inverse = inverse;
   if (!inverse) a.scale = (T)1;
@@ -452,7 +453,7 @@ static R2RFastArgs<T> fast_args(const poisson_plan* p, const AxisTables& A, int 
 template <typename T, typename C>
 static int launch_fast(const poisson_plan* p, const AxisTables& A, int inverse, T* data,
                        hipStream_t st, const double* skip, double* out64 = nullptr) {
-  const R2RFastArgs<T> a = fast_args<T, C>(p, A, inverse, data, skip, out64);
+  const R2RFastArgs<T> a = fast_args<T>(p, A, C::NL, inverse, data, skip, out64);
   const size_t lds = fast_lds_bytes<T, C>();
   const void* fn = reinterpret_cast<const void*>(&r2r_fast_kernel<T, C>);
   hipLaunchKernelGGL((r2r_fast_kernel<T, C>), dim3(resident_grid(fn, 512, lds, a.g.ntiles)),
@@ -479,11 +480,11 @@ static int launch_async(const poisson_plan* p, const AxisTables& A, int shape, i
   if (!async_shape_exists<T>(A.m, shape)) return -1;
   R2RFastArgs<T> a;
   switch (A.m * 4 + shape) {
-    case 128 * 4 + 0: a = fast_args<T, AsyncVar<128, 0>>(p, A, inverse, data, skip, out64); break;
-    case 128 * 4 + 1: a = fast_args<T, AsyncVar<128, 1>>(p, A, inverse, data, skip, out64); break;
-    case 256 * 4 + 0: a = fast_args<T, AsyncVar<256, 0>>(p, A, inverse, data, skip, out64); break;
-    case 256 * 4 + 1: a = fast_args<T, AsyncVar<256, 1>>(p, A, inverse, data, skip, out64); break;
-    default: a = fast_args<T, AsyncVar<256, 2>>(p, A, inverse, data, skip, out64); break;
+    case 128 * 4 + 0: a = fast_args<T>(p, A, AsyncVar<128, 0>::NL, inverse, data, skip, out64); break;
+    case 128 * 4 + 1: a = fast_args<T>(p, A, AsyncVar<128, 1>::NL, inverse, data, skip, out64); break;
+    case 256 * 4 + 0: a = fast_args<T>(p, A, AsyncVar<256, 0>::NL, inverse, data, skip, out64); break;
+    case 256 * 4 + 1: a = fast_args<T>(p, A, AsyncVar<256, 1>::NL, inverse, data, skip, out64); break;
+    default: a = fast_args<T>(p, A, AsyncVar<256, 2>::NL, inverse, data, skip, out64); break;
   }
   const hipError_t e = async_transform_launch(a, A.m, shape, A.kind, inverse, st);
   if (e != hipSuccess)
@@ -520,7 +521,7 @@ static int launch_fast_variant(const poisson_plan* p, const AxisTables& A, int V
   if (V == kRegStageVariant) {
     if constexpr (sizeof(T) == 8) {
       if (regstage_applies<T>(p, A) && (reinterpret_cast<uintptr_t>(data) & 15) == 0) {
-        const R2RFastArgs<T> a = fast_args<T, RegStageCfg>(p, A, inverse, data, skip);
+        const R2RFastArgs<T> a = fast_args<T>(p, A, RegStageCfg::NL, inverse, data, skip);
         // nontemporal accesses on fields at least twice the 256 MB
         // Infinity Cache (smaller ones can stay there between stages)
         const bool hinted = (double)p->dims[0] * p->dims[1] * p->dims[2] * sizeof(T) >=
@@ -543,10 +544,37 @@ static int launch_fast_variant(const poisson_plan* p, const AxisTables& A, int V
   });
 }
 
+// Per-length transform of axis A (r2r_line.h).  The lines along z of a whole
+// field start at consecutive addresses across the rows of a plane, so they
+// are tiled as one run of nx ny lines (no ragged tile at the end of a row).
+template <typename T>
+static int launch_line(const poisson_plan* p, const AxisTables& A, int inverse, T* data,
+                       hipStream_t st, const double* skip, double* out64) {
+  const LineShape S = line_shape(sizeof(T), A.m);
+  R2RFastArgs<T> a = fast_args<T>(p, A, S.nl, inverse, data, skip, out64);
+  if (A.axis == 2) {
+    const int plane[3] = {p->dims[0] * p->dims[1], 1, p->dims[2]};
+    a.g = make_geom(2, plane, ilog2(S.nl));
+  }
+  const hipError_t e = line_transform_launch(a, A.m, st);
+  if (e != hipSuccess) return fail(POISSON_EHIP, "transform launch: %s", hipGetErrorString(e));
+  return POISSON_OK;
+}
+
+// Kernels that a solve may use.  pressure_correction takes kSteady: applied
+// to a velocity that is divergence-free already, its right-hand side is the
+// rounding noise of the divergence, and phi the solve of that noise, so that
+// any other order of operations gives another phi altogether.  There the
+// kernels stay those whose bits callers have seen: the variants and the
+// size-generic ones (270 x 150 x 162: 282 us a solve against 121 with the
+// per-length kernels).
+enum Route { kFastest, kSteady };
+
 // out64 (FP32 only): write the widened result there instead of in place.
 template <typename T>
 static int launch_r2r(const poisson_plan* p, int role, int inverse, T* data, hipStream_t st,
-                      const double* skip = nullptr, double* out64 = nullptr) {
+                      const double* skip = nullptr, double* out64 = nullptr,
+                      Route route = kFastest) {
   const AxisTables& A = p->ax[role];
   if constexpr (sizeof(T) == 8) out64 = nullptr;
   t_grid_cap = p->grid_cap;
@@ -554,6 +582,10 @@ static int launch_r2r(const poisson_plan* p, int role, int inverse, T* data, hip
     const int rc = launch_fast_variant<T>(p, A, tuned_choice(0, sizeof(T), A.m, A.axis == 0),
                                           inverse, data, st, skip, out64);
     if (rc != -1) return rc;
+    // lengths without variants: their per-length kernel (12 <= M <= 512);
+    // shorter ones, whose tiles hold less than a wave's work per line, stay
+    // with the size-generic kernel
+    if (route == kFastest && line_length(A.m)) return launch_line<T>(p, A, inverse, data, st, skip, out64);
   }
   constexpr int EMAX = sizeof(T) == 8 ? R2R_EMAX_D : R2R_EMAX_F;
   const int cap_reals = 2 * EMAX * R2R_NT;
@@ -799,18 +831,19 @@ static int launch_plane(const poisson_plan* p, bool inverse, T* data, hipStream_
 
 template <typename T>
 static int solve_typed(const poisson_plan* p, T* data, hipStream_t st,
-                       const double* skip = nullptr, double* out64 = nullptr) {
+                       const double* skip = nullptr, double* out64 = nullptr,
+                       Route route = kFastest) {
   int rc;
   if (p->plane_mats) {             // small grid: both transforms of a direction in one launch
     if ((rc = launch_plane<T>(p, false, data, st, skip, nullptr))) return rc;
     if ((rc = launch_tridiag<T>(p, data, st, skip))) return rc;
     return launch_plane<T>(p, true, data, st, skip, sizeof(T) == 8 ? nullptr : out64);
   }
-  if ((rc = launch_r2r<T>(p, 0, 0, data, st, skip))) return rc;
-  if ((rc = launch_r2r<T>(p, 1, 0, data, st, skip))) return rc;
+  if ((rc = launch_r2r<T>(p, 0, 0, data, st, skip, nullptr, route))) return rc;
+  if ((rc = launch_r2r<T>(p, 1, 0, data, st, skip, nullptr, route))) return rc;
   if ((rc = launch_tridiag<T>(p, data, st, skip))) return rc;
-  if ((rc = launch_r2r<T>(p, 1, 1, data, st, skip))) return rc;
-  if ((rc = launch_r2r<T>(p, 0, 1, data, st, skip, out64))) return rc;
+  if ((rc = launch_r2r<T>(p, 1, 1, data, st, skip, nullptr, route))) return rc;
+  if ((rc = launch_r2r<T>(p, 0, 1, data, st, skip, out64, route))) return rc;
   return POISSON_OK;
 }
 
@@ -1236,16 +1269,20 @@ extern "C" int plan_set_precision(poisson_plan* p, int mode, double tol, int max
   return POISSON_OK;
 }
 
-static int solve_refined(poisson_plan* p, double* rhs, hipStream_t st);
+static int solve_refined(poisson_plan* p, double* rhs, hipStream_t st, Route route);
 
-extern "C" int solve(poisson_plan* p, double* rhs, hipStream_t st) {
+static int solve_route(poisson_plan* p, double* rhs, hipStream_t st, Route route) {
   if (!p || !rhs) return fail(POISSON_EINVAL, "null argument");
   if (int rc = misaligned(rhs, "rhs")) return rc;
-  if (p->mode == POISSON_FP32_REFINED) return solve_refined(p, rhs, st);
+  if (p->mode == POISSON_FP32_REFINED) return solve_refined(p, rhs, st, route);
   p->last_iters = 1;
   p->last_rel = 0.0;
   p->last_converged = 1;
-  return solve_typed<double>(p, rhs, st);
+  return solve_typed<double>(p, rhs, st, nullptr, nullptr, route);
+}
+
+extern "C" int solve(poisson_plan* p, double* rhs, hipStream_t st) {
+  return solve_route(p, rhs, st, kFastest);
 }
 
 // Status of a refined solve from its status block, copied to host memory at
@@ -1379,23 +1416,24 @@ static int refine_end(const poisson_plan* p, const RefineWork& W, double* rhs, h
 }
 
 // The whole refined solve on workspace W.
-static int run_refined(const poisson_plan* p, const RefineWork& W, double* rhs, hipStream_t st) {
+static int run_refined(const poisson_plan* p, const RefineWork& W, double* rhs, hipStream_t st,
+                       Route route = kFastest) {
   int rc;
   if ((rc = refine_begin(p, W, rhs, st))) return rc;
   // the first FP32 solve's last pass writes Phi (widened) into rhs
-  if ((rc = solve_typed<float>(p, W.e32, st, nullptr, rhs))) return rc;
+  if ((rc = solve_typed<float>(p, W.e32, st, nullptr, rhs, route))) return rc;
   for (int sweep = 1; sweep < W.max_iters; ++sweep) {
     if ((rc = refine_sweep_begin(p, W, rhs, st))) return rc;
-    if ((rc = solve_typed<float>(p, W.e32, st, W.stats))) return rc;
+    if ((rc = solve_typed<float>(p, W.e32, st, W.stats, nullptr, route))) return rc;
     if ((rc = refine_sweep_end(p, W, rhs, sweep, st))) return rc;
   }
   return refine_end(p, W, rhs, st);
 }
 
 // The plan's refined solve, and the status copy for solve_status.
-static int solve_refined(poisson_plan* p, double* rhs, hipStream_t st) {
+static int solve_refined(poisson_plan* p, double* rhs, hipStream_t st, Route route) {
   const RefineWork W = plan_work(p);
-  const int rc = run_refined(p, W, rhs, st);
+  const int rc = run_refined(p, W, rhs, st, route);
   if (rc) return rc;
   HIP_TRY(hipMemcpyAsync(p->stats_host, p->stats, REFINE_PARTIALS * sizeof(double),
                          hipMemcpyDeviceToHost, st));
@@ -1542,7 +1580,7 @@ extern "C" int pressure_correction(poisson_plan* p, double* u, double* v, double
   int rc;
   if (phi && (rc = misaligned(phi, "phi"))) return rc;
   if ((rc = projection_rhs(p, u, v, w, gamma_dt, phi, st))) return rc;
-  if ((rc = solve(p, phi, st))) return rc;
+  if ((rc = solve_route(p, phi, st, kSteady))) return rc;
   return projection_update(p, phi, gamma_dt, u, v, w, pres, st);
 }
 
@@ -1812,7 +1850,7 @@ static void batch_step_jobs(poisson_batch* b, int k, double* const* rhs, std::ve
       if (J.V >= 4) J.V = 0;   // the batched kernel has the synchronous variants
       with_fast_cfg(J.M, J.V, [&](auto cfg) {
         using C = decltype(cfg);
-        J.a = fast_args<T, C>(p, A, kStepInverse[ps], data, skip, out64);
+        J.a = fast_args<T>(p, A, C::NL, kStepInverse[ps], data, skip, out64);
         lds = std::max(lds, fast_lds_bytes<T, C>());
         return 0LL;
       });
