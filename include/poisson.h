@@ -252,7 +252,14 @@ int batch_autotune(poisson_batch* batch, int reps, hipStream_t stream, double* r
  * on the contiguous axis, 6 for FP32 length 512 on the strided axes, 7 for
  * FP64 length 512 on the strided axes, else 4)
  * and variant 0 otherwise; eliminations variant 3 on contiguous lines,
- * variant 1 on strided lines of 384 points and FP32 lines of 256, else 0.  Plans and batches read the
+ * variant 1 on strided lines of 384 points and FP32 lines of 256, else 0.
+ * Beside the variants, every length has kernels of its own: solves use them
+ * for the lengths without variants, and for strided eliminations of the
+ * others while their entry is neither set by hand nor tuned (the autotuner
+ * times them too, and solves keep them where they beat every variant; the
+ * entry then still names the fastest variant).  pressure_correction always
+ * runs the variants and the size-generic kernels, so that its results keep
+ * their bits.  Plans and batches read the
  * table when they launch (batches when they are bound; batches use the
  * synchronous variants only: transforms 0-3, elimination 0-1). */
 

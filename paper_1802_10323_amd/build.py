@@ -15,7 +15,8 @@ LIB = os.path.join(HERE, "libpoisson_hip.so")
 LINE_PARTS = 8      # objects of r2r_line_part.hip, each with its share of the lengths
 # (source, extra flags, object name)
 UNITS = [(name, [], name + ".o")
-         for name in ("poisson.hip", "r2r_async.hip", "r2r_async_wide.hip", "tri_async.hip")]
+         for name in ("poisson.hip", "r2r_async.hip", "r2r_async_wide.hip", "tri_async.hip",
+                      "tri_line.hip")]
 UNITS += [("r2r_line_part.hip", [f"-DPOISSON_LINE_PART_INDEX={i}"], f"r2r_line_part{i}.hip.o")
           for i in range(LINE_PARTS)]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -45,6 +45,13 @@ hipError_t regstage_launch(const R2RFastArgs<double>& a, int kind, int inverse, 
 hipError_t direct_elimination_launch(const TriFastArgs<double>& a, int n, hipStream_t stream);
 hipError_t direct_elimination_launch(const TriFastArgs<float>& a, int n, hipStream_t stream);
 
+// The elimination of lines of any length with a chunking (tri_line_shape in
+// tri_line.h; tri_line.hip), the geometry made for tiles of 512 / P lines, the
+// coefficient tables laid out by virtual row.  hipErrorInvalidValue if the
+// length has no chunking.
+hipError_t line_elimination_launch(const TriFastArgs<double>& a, int n, hipStream_t stream);
+hipError_t line_elimination_launch(const TriFastArgs<float>& a, int n, hipStream_t stream);
+
 // The kernels of AsyncBudget<double, FastVar<256, 0>, kind>::WIDE
 // (r2r_async_wide.hip).
 hipError_t async_wide_launch(const R2RFastArgs<double>& a, int kind, int inverse,

@@ -22,6 +22,7 @@
 #include "r2r_fast.h"
 #include "tridiag_kernel.h"
 #include "tri_fast.h"
+#include "tri_line.h"
 #include "batch_kernels.h"
 #include "async_launch.h"
 #include "line_launch.h"
@@ -168,11 +169,15 @@ struct poisson_plan {
   AxisTables ax[2];
   // elimination axis tables
   size_t off_tri_d = 0, off_tri_f = 0;     // a, b, c, w   (4 n_s)
-  // Lines whose length has no size-specialised kernel are run in the kernel
-  // of the next specialised length pad_n (0: not padded), with the tables
-  // extended by decoupled rows (see plan_create).
+  // Lines whose length has no size-specialised kernel run, where the steady
+  // route is asked for, in the kernel of the next specialised length pad_n (0:
+  // not padded), with the tables extended by decoupled rows (see plan_create).
   int pad_n = 0;
   size_t off_tri_pad = 0;                  // a, b, c, w   (4 pad_n), FP64
+  // The chunks of tri_line.h: line_rows = P * RPC virtual rows (0: the line is
+  // too short for any chunking).
+  int line_rows = 0;
+  size_t off_tri_line = 0;                 // a, b, c, w   (4 line_rows), FP64
   size_t off_lam_d = 0, off_lam_f = 0;     // lamu, lamv
   size_t off_ops[3] = {0, 0, 0};           // per axis: a, b, c, h (FP64, residual)
   size_t off_proj[3] = {0, 0, 0};          // per axis: 1/h (n), 1/centre distance (n + 1)
@@ -283,12 +288,23 @@ static int default_choice(int family, int bytes, int n, int layout) {
   return kAsyncVariant + shape;
 }
 
-static int tuned_choice(int family, int bytes, int n, int layout) {
+// Per-length form (r2r_line.h, tri_line.h) in the variant table: used where
+// nothing was tuned or set, and where the autotuner found it faster than every
+// variant (the table then holds the fastest variant with kLineFaster added).
+static constexpr int kLineFaster = 256;
+
+// The entry as it stands, or -1.
+static int tuned_entry(int family, int bytes, int n, int layout) {
   int dev = 0;
   (void)hipGetDevice(&dev);
   std::lock_guard<std::mutex> lk(g_tune_mu);
   const auto it = g_tune.find(std::make_tuple(dev, family, bytes, n, layout));
-  return it == g_tune.end() ? default_choice(family, bytes, n, layout) : it->second;
+  return it == g_tune.end() ? -1 : it->second;
+}
+
+static int tuned_choice(int family, int bytes, int n, int layout) {
+  const int e = tuned_entry(family, bytes, n, layout);
+  return e < 0 ? default_choice(family, bytes, n, layout) : e & (kLineFaster - 1);
 }
 
 static void set_tuned_choice(int family, int bytes, int n, int layout, int v) {
@@ -653,6 +669,57 @@ static TriFastArgs<T> tri_fast_args(const poisson_plan* p, T* data, const double
   return a;
 }
 
+// True if lines of n points have size-specialised elimination kernels.
+static bool tri_fast_length(int n) {
+  return with_tri_cfg(n, 0, [](auto) { return 0LL; }) == 0;
+}
+
+// Elimination in the chunks of tri_line.h.
+template <typename T>
+static int launch_tri_line(const poisson_plan* p, T* data, hipStream_t st, const double* skip) {
+  const int n = p->dims[p->s];
+  const TriLineShape S = tri_line_shape(n);
+  TriFastArgs<T> a{};
+  a.data = data;
+  a.g = make_geom(p->s, p->dims, ilog2(S.nl));
+  a.periodic = p->s_periodic;
+  a.singular = p->singular;
+  a.nu = p->nu;
+  a.nv = p->nv;
+  const size_t N = (size_t)p->line_rows;
+  const double* tri = reinterpret_cast<const double*>(p->dtab + p->off_tri_line);
+  a.nreal = n;
+  a.a = tri;
+  a.b = tri + N;
+  a.c = tri + 2 * N;
+  a.w = tri + 3 * N;
+  const double* lam = reinterpret_cast<const double*>(p->dtab + p->off_lam_d);
+  a.lamu = lam;
+  a.lamv = lam + p->nu;
+  a.skip = skip;
+  const hipError_t e = line_elimination_launch(a, n, st);
+  if (e != hipSuccess) return fail(POISSON_EHIP, "elimination launch: %s", hipGetErrorString(e));
+  return POISSON_OK;
+}
+
+// True if the plan's lines take the chunks of tri_line.h: every length without
+// size-specialised kernels (they ran padded to the next one, or, singular and
+// periodic lines, in the size-generic kernel), and strided lines of the
+// specialised lengths where no variant was set or tuned to be faster.
+// Contiguous specialised lines keep the direct form (no LDS tile), lines of
+// 32 and 48 points of a small grid their 16-lane chunks (more lanes at work on
+// so few lines).  Measured on 512 x ny x n fields of 2^25 points, singular:
+// n = 100 1.38 -> 5.2 TB/s, 144 1.77 -> 5.9, 250 2.19 -> 5.9, 400 1.87 -> 4.4;
+// regular: 191 (padded before) 4.50 -> 5.9.
+template <typename T>
+static bool tri_line_applies(const poisson_plan* p) {
+  const int n = p->dims[p->s];
+  if (!p->line_rows || (p->plane_mats && (n == 32 || n == 48))) return false;
+  if (!tri_fast_length(n)) return true;
+  const int e = tuned_entry(1, sizeof(T), n, p->s == 0);
+  return e < 0 ? p->s != 0 : (e & kLineFaster) != 0;
+}
+
 template <typename T, int RPC, int P>
 static int launch_tri_fast(const poisson_plan* p, T* data, hipStream_t st, const double* skip) {
   using L = TriFastLayout<T, RPC, P>;
@@ -731,11 +798,6 @@ static int launch_tri_variant(const poisson_plan* p, int V, T* data, hipStream_t
   });
 }
 
-// True if lines of n points have size-specialised elimination kernels.
-static bool tri_fast_length(int n) {
-  return with_tri_cfg(n, 0, [](auto) { return 0LL; }) == 0;
-}
-
 // Complex length M of the size-specialised transform kernel for axis A, or
 // 0 if its length has none, among the lengths the batched kernel takes
 // (single solves also have 72, 80, 144 and 160).
@@ -749,8 +811,9 @@ static int r2r_fast_length(const AxisTables& A) {
 
 template <typename T>
 static int launch_tridiag(const poisson_plan* p, T* data, hipStream_t st,
-                          const double* skip = nullptr) {
+                          const double* skip = nullptr, Route route = kFastest) {
   t_grid_cap = p->grid_cap;
+  if (route == kFastest && tri_line_applies<T>(p)) return launch_tri_line<T>(p, data, st, skip);
   if (p->pad_n) {   // padded lines: the plain chunked kernel of length pad_n
     return (int)with_tri_cfg(p->pad_n, 0, [&](auto cfg) {
       using C = decltype(cfg);
@@ -841,7 +904,7 @@ static int solve_typed(const poisson_plan* p, T* data, hipStream_t st,
   }
   if ((rc = launch_r2r<T>(p, 0, 0, data, st, skip, nullptr, route))) return rc;
   if ((rc = launch_r2r<T>(p, 1, 0, data, st, skip, nullptr, route))) return rc;
-  if ((rc = launch_tridiag<T>(p, data, st, skip))) return rc;
+  if ((rc = launch_tridiag<T>(p, data, st, skip, route))) return rc;
   if ((rc = launch_r2r<T>(p, 1, 1, data, st, skip, nullptr, route))) return rc;
   if ((rc = launch_r2r<T>(p, 0, 1, data, st, skip, out64, route))) return rc;
   return POISSON_OK;
@@ -1122,6 +1185,30 @@ extern "C" poisson_plan* plan_create_helmholtz(int nx, int ny, int nz, double dx
           break;
         }
       }
+    }
+    // Rows laid out for the chunks of tri_line.h: virtual rows, a missing one
+    // decoupled (diagonal -1, weight 0).  In the place of the diagonal the row
+    // sum a + b + c: the shift, and at a Dirichlet wall its ghost-cell term.
+    // The sum is exact (a two-sum of a and c), so that the rows solved are
+    // those of the residual and the other kernels to the last bit.
+    if (!p->generic_tri && tri_line_shape(ns_).p) {
+      const TriLineShape S = tri_line_shape(ns_);
+      const int N = S.rpc * S.p, missing = N - ns_;
+      std::vector<double> t(4 * (size_t)N, 0.0);
+      for (int k = 0; k < N; ++k) {
+        const int ch = k / S.rpc;
+        if (ch < missing && k == ch * S.rpc) {
+          t[N + k] = -1.0;
+          continue;
+        }
+        const int row = k - std::min(ch + 1, missing);
+        for (int q = 0; q < 4; ++q) t[(size_t)q * N + k] = tri[(size_t)q * ns_ + row];
+        const double a = tri[row], c = tri[2 * ns_ + row], ac = a + c, c1 = ac - a;
+        const double low = (a - (ac - c1)) + (c - c1);   // a + c - fl(a + c)
+        t[N + k] = (tri[ns_ + row] + ac) + low;
+      }
+      p->line_rows = N;
+      p->off_tri_line = push(t.data(), t.size() * sizeof(double));
     }
     if (p->pad_n) {
       const int N = p->pad_n;
@@ -2220,6 +2307,13 @@ static int autotune_typed(poisson_plan* p, double* scratch, int reps, hipStream_
       if (rc) return rc;
       if (report) report[2 * kFastVariants + V] = ms;
       if (ms < best_ms) { best_ms = ms; best = V; }
+    }
+    if (p->line_rows) {   // the per-length form, if it beats them all
+      if ((rc = reset())) return rc;
+      const double ms = time_launches(
+          st, reps, [&]() { return launch_tri_line<T>(p, data, st, nullptr); }, rc);
+      if (rc) return rc;
+      if (ms < best_ms) best |= kLineFaster;
     }
     set_tuned_choice(1, sizeof(T), n, p->s == 0, best);
   }

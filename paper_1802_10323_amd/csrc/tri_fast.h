@@ -91,8 +91,11 @@ __device__ __forceinline__ int tri_fast_slot(int p, int ll) {
 }
 
 // Tile load: global -> LDS; all global loads of a thread are issued before
-// its first LDS write.  Strided layout: line tid mod NL, points
-// tid / NL + i P; contiguous layout: element tid + i NT of the tile's run.
+// its first LDS write.  Strided layout: line tid mod NL, the rows of chunk
+// tid / NL in order, so that a row's address and LDS slot follow from the
+// row before by a uniform step (with rows tid / NL + i P instead, every
+// element took a division by RPC and a 64-bit product, on the way in and on
+// the way out); contiguous layout: element tid + i NT of the tile's run.
 // LAY >= 0: the layout as a constant (0 strided, 1 contiguous); -1: `layout`.
 template <typename T, int RPC, int P, int LAY = -1>
 __device__ __noinline__ void tri_fast_load(lptr<T> lds, gptr<const T> data, long long base,
@@ -101,17 +104,18 @@ __device__ __noinline__ void tri_fast_load(lptr<T> lds, gptr<const T> data, long
   using L = TriFastLayout<T, RPC, P>;
   T buf[RPC];
   if ((LAY >= 0 ? LAY : layout) == 0) {
-    const int l = tid % L::NL, q = tid / L::NL;
+    const int l = tid % L::NL, ch = tid / L::NL, r0 = ch * RPC;
+    const gptr<const T> src = data + (base + r0 * sp);
     if (nreal >= L::N) {   // whole lines (uniform): no row mask
 #pragma unroll
-      for (int i = 0; i < RPC; ++i) buf[i] = base >= 0 ? data[base + (q + i * P) * sp] : (T)0;
+      for (int i = 0; i < RPC; ++i) buf[i] = base >= 0 ? src[i * sp] : (T)0;
     } else {               // a padded line: rows past nreal read as 0
 #pragma unroll
-      for (int i = 0; i < RPC; ++i)
-        buf[i] = base >= 0 && q + i * P < nreal ? data[base + (q + i * P) * sp] : (T)0;
+      for (int i = 0; i < RPC; ++i) buf[i] = base >= 0 && r0 + i < nreal ? src[i * sp] : (T)0;
     }
+    const lptr<T> dst = lds + ch * L::CP + l;
 #pragma unroll
-    for (int i = 0; i < RPC; ++i) lds[tri_fast_slot<T, RPC, P>(q + i * P, l)] = buf[i];
+    for (int i = 0; i < RPC; ++i) dst[i * L::NLP] = buf[i];
   } else {
     if (nreal >= L::N) {   // whole lines (uniform): one contiguous run
 #pragma unroll
@@ -142,17 +146,19 @@ __device__ __forceinline__ void tri_fast_store_body(lptr<const T> lds, gptr<T> d
                                                     int nreal) {
   using L = TriFastLayout<T, RPC, P>;
   T buf[RPC];
-  if (layout == 0) {
-    const int l = tid % L::NL, q = tid / L::NL;
+  if (layout == 0) {   // (as tri_fast_load)
+    const int l = tid % L::NL, ch = tid / L::NL, r0 = ch * RPC;
+    const lptr<const T> src = lds + ch * L::CP + l;
+    const gptr<T> dst = data + (base + r0 * sp);
 #pragma unroll
-    for (int i = 0; i < RPC; ++i) buf[i] = lds[tri_fast_slot<T, RPC, P>(q + i * P, l)];
+    for (int i = 0; i < RPC; ++i) buf[i] = src[i * L::NLP];
     if (base >= 0 && nreal >= L::N) {
 #pragma unroll
-      for (int i = 0; i < RPC; ++i) data[base + (q + i * P) * sp] = buf[i];
+      for (int i = 0; i < RPC; ++i) dst[i * sp] = buf[i];
     } else if (base >= 0) {   // a padded line: rows past nreal are not stored
 #pragma unroll
       for (int i = 0; i < RPC; ++i)
-        if (q + i * P < nreal) data[base + (q + i * P) * sp] = buf[i];
+        if (r0 + i < nreal) dst[i * sp] = buf[i];
     }
   } else {
 #pragma unroll
@@ -193,31 +199,39 @@ __device__ __forceinline__ T line_sum(T v) {
   return v;
 }
 
-// Cyclic rotation inside a row of 16 lanes (DPP row_ror: lane i reads lane
-// (i - R) mod 16 of its row); a VALU operation, no LDS traffic.
-template <int R>
-__device__ __forceinline__ int dpp_ror(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, 0x120 + R, 0xF, 0xF, false);
+// Move between lanes by a DPP control: a VALU operation, no LDS traffic.
+template <int CTRL>
+__device__ __forceinline__ int dpp_mov(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
 }
-template <int R>
-__device__ __forceinline__ float dpp_ror(float v) {
-  return __builtin_bit_cast(float, dpp_ror<R>(__builtin_bit_cast(int, v)));
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float v) {
+  return __builtin_bit_cast(float, dpp_mov<CTRL>(__builtin_bit_cast(int, v)));
 }
-template <int R>
-__device__ __forceinline__ double dpp_ror(double v) {
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov(double v) {
   const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-  const unsigned lo = (unsigned)dpp_ror<R>((int)(unsigned)b);
-  const unsigned hi = (unsigned)dpp_ror<R>((int)(unsigned)(b >> 32));
+  const unsigned lo = (unsigned)dpp_mov<CTRL>((int)(unsigned)b);
+  const unsigned hi = (unsigned)dpp_mov<CTRL>((int)(unsigned)(b >> 32));
   return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+// Cyclic rotation inside a row of 16 lanes (row_ror: lane i reads lane
+// (i - R) mod 16 of its row).
+template <int R, typename T>
+__device__ __forceinline__ T dpp_ror(T v) {
+  return dpp_mov<0x120 + R>(v);
 }
 
 // v of the lane ST places before (AFTER = false) or after (AFTER = true)
 // this one, cyclically within its group of P lanes.  A group of 16 lanes is
-// one DPP row; larger groups go through ds_bpermute.
+// one DPP row, one of 4 a quad; other groups go through ds_bpermute.
 template <int P, int ST, bool AFTER, typename T>
 __device__ __forceinline__ T group_rot(T v, int gbase, int c) {
   if constexpr (P == 16) {
     return dpp_ror<AFTER ? 16 - ST : ST>(v);
+  } else if constexpr (P == 4) {   // rotation of a quad
+    constexpr int R = AFTER ? 4 - ST : ST;   // lane i reads lane (i - R) mod 4
+    return dpp_mov<((4 - R) & 3) | ((5 - R) & 3) << 2 | ((6 - R) & 3) << 4 | ((7 - R) & 3) << 6>(v);
   } else {
     return __shfl(v, gbase + ((AFTER ? c + ST : c - ST) & (P - 1)), 64);
   }
@@ -228,9 +242,20 @@ __device__ __forceinline__ T group_rot(T v, int gbase, int c) {
 // equation of lane c-ST and u times that of lane c+ST, doubling the coupling
 // distance; outside a non-periodic line the neighbour is the identity
 // equation x = 0.
-template <typename T, int P, int ST>
+//
+// EXIT: stop once every coupling of the wave's lines is below 2^-64: a further
+// step would change a right-hand side by less than 2^-64 of its neighbours',
+// far below rounding.  A step squares the couplings, which start near
+// rho^RPC, rho the decay per row of the line's Green's function (about 0.2
+// where |mu| h^2 = 4), so that most waves need two steps, not log2 P.
+template <typename T, int P, int ST, bool EXIT = false>
 __device__ __forceinline__ void pcr(T& l, T& u, T& r, int c, int gbase, int periodic) {
   if constexpr (ST < P) {
+    if constexpr (EXIT) {
+      const T tiny = (T)0x1p-64;
+      // (an infinity or a NaN still reaches every row of its line)
+      if (__all(__builtin_fabs(l) < tiny && __builtin_fabs(u) < tiny && __builtin_isfinite(r))) return;
+    }
     T lm = group_rot<P, ST, false>(l, gbase, c);
     T um = group_rot<P, ST, false>(u, gbase, c);
     T rm = group_rot<P, ST, false>(r, gbase, c);
@@ -244,7 +269,7 @@ __device__ __forceinline__ void pcr(T& l, T& u, T& r, int c, int gbase, int peri
     l = -l * lm * inv;
     u = -u * up * inv;
     r = rn;
-    pcr<T, P, 2 * ST>(l, u, r, c, gbase, periodic);
+    pcr<T, P, 2 * ST, EXIT>(l, u, r, c, gbase, periodic);
   }
 }
 
@@ -265,9 +290,14 @@ __device__ __forceinline__ void pcr(T& l, T& u, T& r, int c, int gbase, int peri
 // the tile), coefficient tables ca/cb/cc/cw in LDS laid out [row in
 // chunk][chunk], shift mu, and the singular-line flags.  FENCE: keep each
 // row's coefficient loads in its own step (long chunks held in the tile).
-template <int RPC, int P, bool FENCE, typename Get, typename Set>
+// RAG: where `absent`, the chunk has no row 0 (RPC - 1 rows; its row 0 holds
+// right-hand side 0, weight 0, c = 0): the row then stands for the previous
+// chunk's interface unknown, so that row 1 couples to that; the reduction may
+// end early (pcr, EXIT).
+template <int RPC, int P, bool FENCE, bool RAG = false, typename Get, typename Set>
 __device__ __forceinline__ void tri_line_solve(Get xget, Set xset, lptr<const double> coef, int c,
-                                               double mu, int sing, int wave_sing, int periodic) {
+                                               double mu, int sing, int wave_sing, int periodic,
+                                               bool absent = false) {
   using R = double;
   constexpr int N = RPC * P;
   const int lane = threadIdx.x & 63;
@@ -291,6 +321,8 @@ __device__ __forceinline__ void tri_line_solve(Get xget, Set xset, lptr<const do
       const R mean = swf / sw;
 #pragma unroll
       for (int i = 0; i < RPC; ++i) xset(i, xget(i) - mean);
+      if constexpr (RAG)
+        if (absent) xset(0, 0.0);
     }
   }
 
@@ -298,15 +330,38 @@ __device__ __forceinline__ void tri_line_solve(Get xget, Set xset, lptr<const do
   // qv = spike of the previous interface, cp = c / pivot
   constexpr int NI = RPC - 1;
   R cp[NI], qv[NI];
-  R r = fast_rcp(cb[c] + mu);
-  R xp = xget(0) * r;
-  xset(0, xp);
-  qv[0] = ca[c] * r;
-  cp[0] = cc[c] * r;
+  R r, xp;
+  R s = 1;   // RAG: 1 + cp of the row before (the previous interface: 1)
+  if constexpr (RAG) {
+    // cb holds the row sums a + b + c: pivot_i = t_i - c_i with
+    // t_i = sum_i + mu - a_i (1 + cp_{i-1}), and 1 + cp_i = t_i / pivot_i.  Every
+    // term of t_i has the same sign, so nothing cancels; b_i + mu - a_i cp_{i-1}
+    // loses a digit for every three rows where |mu| h^2 is small.
+    const R t = cb[c] + mu - ca[c];
+    const R c0 = cc[c];
+    r = fast_rcp(t - c0);
+    xp = xget(0) * r;
+    xset(0, xp);
+    qv[0] = absent ? (R)-1 : ca[c] * r;   // a missing row stands for I_prev
+    cp[0] = c0 * r;
+    s = absent ? (R)1 : t * r;
+  } else {
+    r = fast_rcp(cb[c] + mu);
+    xp = xget(0) * r;
+    xset(0, xp);
+    qv[0] = ca[c] * r;
+    cp[0] = cc[c] * r;
+  }
 #pragma unroll
   for (int i = 1; i < NI; ++i) {
     const R ai = ca[i * P + c], bi = cb[i * P + c], ci = cc[i * P + c];
-    r = fast_rcp(bi + mu - ai * cp[i - 1]);
+    if constexpr (RAG) {
+      const R t = bi + mu - ai * s;
+      r = fast_rcp(t - ci);
+      s = t * r;
+    } else {
+      r = fast_rcp(bi + mu - ai * cp[i - 1]);
+    }
     xp = (xget(i) - ai * xp) * r;
     xset(i, xp);
     qv[i] = -ai * qv[i - 1] * r;
@@ -318,6 +373,9 @@ __device__ __forceinline__ void tri_line_solve(Get xget, Set xset, lptr<const do
   R yf = yl, vf = vl, wf = wl;
 #pragma unroll
   for (int i = NI - 2; i >= 0; --i) {
+    if constexpr (RAG) {
+      if (i == 0 && absent) continue;   // row 1 is the chunk's first
+    }
     yf = xget(i) - cp[i] * yf;
     vf = qv[i] - cp[i] * vf;
     wf = -cp[i] * wf;
@@ -330,11 +388,13 @@ __device__ __forceinline__ void tri_line_solve(Get xget, Set xset, lptr<const do
   const R yf_n = group_rot<P, 1, true>(yf, gbase, c);
   const R vf_n = group_rot<P, 1, true>(vf, gbase, c);
   const R wf_n = group_rot<P, 1, true>(wf, gbase, c);
-  const R inv = fast_rcp(be - ae * wl - ce * vf_n);
+  // (RAG: be is the row sum; 1 + wl = s)
+  const R inv = RAG ? (sing && c == P - 1 ? (R)1 : fast_rcp(be - ae * s - ce * ((R)1 + vf_n)))
+                    : fast_rcp(be - ae * wl - ce * vf_n);
   R lq = -ae * vl * inv;
   R uq = -ce * wf_n * inv;
   R rq = (fe - ae * yl - ce * yf_n) * inv;
-  pcr<R, P, 1>(lq, uq, rq, c, gbase, periodic);
+  pcr<R, P, 1, RAG>(lq, uq, rq, c, gbase, periodic);
   // after the reduction the remaining couplings point back at this unknown
   const R Ic = periodic ? rq / ((R)1 + lq + uq) : rq;
   R Ip = group_rot<P, 1, false>(Ic, gbase, c);
@@ -429,7 +489,7 @@ template <typename T, int RPC, int P, int LAY = -1>
 __device__ __forceinline__ void tri_fast_tile(lptr<T> lds, lptr<const double> coef,
                                               const TriFastArgs<T>& A, int tile, int tid) {
   using L = TriFastLayout<T, RPC, P>;
-  constexpr int N = L::N, NL = L::NL;
+  constexpr int NL = L::NL;
   LineGeom g = A.g;
   if (LAY >= 0) g.layout = LAY;   // a constant for the inlined geometry helpers
   const int c = tid % P;        // chunk of this thread
