@@ -254,12 +254,12 @@ int batch_autotune(poisson_batch* batch, int reps, hipStream_t stream, double* r
  * and variant 0 otherwise; eliminations variant 3 on contiguous lines,
  * variant 1 on strided lines of 384 points and FP32 lines of 256, else 0.
  * Beside the variants, every length has kernels of its own: solves use them
- * for the lengths without variants, and for strided eliminations of the
- * others while their entry is neither set by hand nor tuned (the autotuner
- * times them too, and solves keep them where they beat every variant; the
- * entry then still names the fastest variant).  pressure_correction always
- * runs the variants and the size-generic kernels, so that its results keep
- * their bits.  Plans and batches read the
+ * for the lengths without variants, and for the others (transforms other than
+ * length 512, strided eliminations) while their entry is neither set by hand
+ * nor tuned.  The autotuner times them too, and solves keep them where they
+ * beat every variant; the entry then still names the fastest variant.
+ * pressure_correction always runs the variants and the size-generic kernels,
+ * so that its results keep their bits.  Plans and batches read the
  * table when they launch (batches when they are bound; batches use the
  * synchronous variants only: transforms 0-3, elimination 0-1). */
 

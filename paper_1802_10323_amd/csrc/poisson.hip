@@ -566,7 +566,7 @@ static int launch_fast_variant(const poisson_plan* p, const AxisTables& A, int V
 template <typename T>
 static int launch_line(const poisson_plan* p, const AxisTables& A, int inverse, T* data,
                        hipStream_t st, const double* skip, double* out64) {
-  const LineShape S = line_shape(sizeof(T), A.m);
+  const LineShape S = line_shape(sizeof(T), A.m, A.axis == 0);
   R2RFastArgs<T> a = fast_args<T>(p, A, S.nl, inverse, data, skip, out64);
   if (A.axis == 2) {
     const int plane[3] = {p->dims[0] * p->dims[1], 1, p->dims[2]};
@@ -575,6 +575,20 @@ static int launch_line(const poisson_plan* p, const AxisTables& A, int inverse, 
   const hipError_t e = line_transform_launch(a, A.m, st);
   if (e != hipSuccess) return fail(POISSON_EHIP, "transform launch: %s", hipGetErrorString(e));
   return POISSON_OK;
+}
+
+// True if axis A takes its per-length kernel (12 <= M <= 512; a shorter line's
+// tile holds less than a wave's work): every length without variants, and the
+// others where no variant was set or tuned to be faster (length 512 has the
+// staging forms only).  Gains over the variants on fields of 2^25 points, along
+// x / y: n = 128 4.6 / 4.9 -> 5.8 / 5.3 TB/s, 192 4.9 / 5.1 -> 6.4 / 6.1, 256
+// 5.6 / 5.4 -> 6.1 / 5.8, 288 3.5 / 3.6 -> 5.8 / 5.7.
+template <typename T>
+static bool line_applies(const AxisTables& A) {
+  if (!line_length(A.m)) return false;
+  if (with_fast_cfg(A.m, 0, [](auto) { return 0LL; }) != 0) return true;
+  const int e = tuned_entry(0, sizeof(T), A.m, A.axis == 0);
+  return e < 0 || (e & kLineFaster) != 0;
 }
 
 // Kernels that a solve may use.  pressure_correction takes kSteady: applied
@@ -595,13 +609,11 @@ static int launch_r2r(const poisson_plan* p, int role, int inverse, T* data, hip
   if constexpr (sizeof(T) == 8) out64 = nullptr;
   t_grid_cap = p->grid_cap;
   if (!p->generic_r2r && !node_pair(A.kind)) {
+    if (route == kFastest && line_applies<T>(A))
+      return launch_line<T>(p, A, inverse, data, st, skip, out64);
     const int rc = launch_fast_variant<T>(p, A, tuned_choice(0, sizeof(T), A.m, A.axis == 0),
                                           inverse, data, st, skip, out64);
     if (rc != -1) return rc;
-    // lengths without variants: their per-length kernel (12 <= M <= 512);
-    // shorter ones, whose tiles hold less than a wave's work per line, stay
-    // with the size-generic kernel
-    if (route == kFastest && line_length(A.m)) return launch_line<T>(p, A, inverse, data, st, skip, out64);
   }
   constexpr int EMAX = sizeof(T) == 8 ? R2R_EMAX_D : R2R_EMAX_F;
   const int cap_reals = 2 * EMAX * R2R_NT;
@@ -899,7 +911,7 @@ static int solve_typed(const poisson_plan* p, T* data, hipStream_t st,
   int rc;
   if (p->plane_mats) {             // small grid: both transforms of a direction in one launch
     if ((rc = launch_plane<T>(p, false, data, st, skip, nullptr))) return rc;
-    if ((rc = launch_tridiag<T>(p, data, st, skip))) return rc;
+    if ((rc = launch_tridiag<T>(p, data, st, skip, route))) return rc;
     return launch_plane<T>(p, true, data, st, skip, sizeof(T) == 8 ? nullptr : out64);
   }
   if ((rc = launch_r2r<T>(p, 0, 0, data, st, skip, nullptr, route))) return rc;
@@ -940,7 +952,7 @@ static int build_plane_matrices(poisson_plan* p) {
       q.ax[r].axis = 0;
       q.grid_cap = 0;
       q.plane_mats = nullptr;
-      if ((rc = launch_r2r<double>(&q, r, inv, tmp, nullptr))) break;
+      if ((rc = launch_r2r<double>(&q, r, inv, tmp, nullptr, nullptr, nullptr, kSteady))) break;
       const size_t off = h.size();
       h.resize(off + mm);
       if (hipMemcpy(h.data() + off, tmp, mm * sizeof(double), hipMemcpyDeviceToHost) != hipSuccess)
@@ -2290,6 +2302,16 @@ static int autotune_typed(poisson_plan* p, double* scratch, int reps, hipStream_
       if (rc) return rc;
       if (report) report[role * kFastVariants + V] = ms;
       if (ms < best_ms) { best_ms = ms; best = V; }
+    }
+    if (line_length(A.m)) {   // the per-length form, if it beats them all
+      if ((rc = reset())) return rc;
+      const double ms = time_launches(st, reps, [&]() -> int {
+        int r = launch_line<T>(p, A, 0, data, st, nullptr, nullptr);
+        if (!r) r = launch_line<T>(p, A, 1, data, st, nullptr, nullptr);
+        return r;
+      }, rc);
+      if (rc) return rc;
+      if (ms < best_ms) best |= kLineFaster;
     }
     set_tuned_choice(0, sizeof(T), A.m, A.axis == 0, best);
   }

@@ -1,6 +1,6 @@
 // r2r_line.h - the batched real-to-real transforms (Table 2 / Table 1) for
-// every supported length n = 2M with 12 <= M <= 512 (M = 2^a 3^b 5^c), each
-// length compiled with its own radices, tile and loop bounds.
+// every supported length n = 2M with 12 <= M <= 512 (M = 2^a 3^b 5^c) but n =
+// 512, each length compiled with its own radices, tile and loop bounds.
 //
 // Same mathematics as r2r_kernel.h: one complex FFT of length M per line and
 // the pre/post steps of the type.  What differs from that size-generic
@@ -22,12 +22,11 @@
 // Bound: HBM, like every stage (16 B per point in FP64).  The size-generic
 // kernel ran at 1.7-2.4 TB/s (64-bit address arithmetic and run-time
 // divisions in every element, each stage a call that drains the loads and
-// stores in flight); this one, on one box, on fields of 2^25 points, forward /
-// backward: n = 270 along x 1.64 / 1.68 -> 5.07 / 5.09 TB/s and along y
-// 1.72 / 1.76 -> 4.20 / 4.23; n = 640 (DCT-II) along x 1.87 / 1.90 -> 4.91 /
-// 4.95 and along y 1.88 / 1.91 -> 4.48 / 4.44; n = 1024 along x 2.45 / 2.45 ->
-// 4.24 / 4.33 and along y 2.44 / 2.39 -> 4.22 / 4.13.  Whole solves: 270 x 150
-// x 162 281 -> 121 us, 1024 x 640 x 320 8.15 -> 5.02 ms.
+// stores in flight); this one on fields of 2^25 points, the types and both
+// directions averaged, along x / y: n = 192 6.4 / 6.1 TB/s, 250 5.6 / 4.9
+// (generic 2.2), 288 5.8 / 5.7, 480 6.0 / 5.9 (2.3), 640 5.2 / 4.7 (1.9), 1024
+// 4.7 / 4.4 (2.4; its tile leaves room for one block to a CU).  Whole solves: 270
+// x 150 x 162 281 -> 114 us, 1024 x 640 x 320 8.16 -> 3.77 ms.
 //
 // Three pipelines: PIPE_FWD (real DFT, DCT-II, DST-II), PIPE_INV (their
 // inverses), PIPE_IV (DCT-IV, DST-IV, both directions).  Two layouts: strided
@@ -144,10 +143,11 @@ constexpr int line_pass_cost(int m, int r, int qt) { return (m / r + qt - 1) / q
 // As few passes as the radices allow (one LDS round trip and two barriers
 // each), then the fewest idle thread slots; the largest radix first, since
 // the first pass needs no twiddles.
-constexpr RadixPlan line_plan(int m, int qt) {
+// rmax: the largest radix whose values fit the registers.
+constexpr RadixPlan line_plan(int m, int qt, int rmax) {
   RadixPlan best{0, {0}};
   int cost = 1 << 30;
-  for (int r1 = 25; r1 >= 2; --r1)
+  for (int r1 = rmax; r1 >= 2; --r1)
     if (line_radix(r1) && m % r1 == 0 && line_radix(m / r1) && m / r1 <= r1) {
       const int c = line_pass_cost(m, r1, qt) + line_pass_cost(m, m / r1, qt) + 4 * r1;
       if (c < cost) { cost = c; best = RadixPlan{2, {r1, m / r1}}; }
@@ -166,10 +166,10 @@ constexpr RadixPlan line_plan(int m, int qt) {
 }
 
 // Tile: NL lines, NT threads, QT = NT / NL threads per line.
-template <int M_, int NL_, int NT_>
+template <int M_, int NL_, int NT_, int RMAX_>
 struct LineCfg {
   static constexpr int M = M_, NL = NL_, NT = NT_, QT = NT_ / NL_;
-  static constexpr RadixPlan plan = line_plan(M_, QT);
+  static constexpr RadixPlan plan = line_plan(M_, QT, RMAX_);
   static_assert(plan.count > 0, "length without a radix plan");
   static_assert(QT * NL == NT && (NL & (NL - 1)) == 0, "whole threads per line");
 };
@@ -183,7 +183,14 @@ struct LineLayout {
   static constexpr int TILE = N * NLP;
   static constexpr int EP = (N + QT - 1) / QT;              // points per thread
   static constexpr int EC = (M + QT - 1) / QT;              // complex values per thread
-  static constexpr int SP = (M / 2 + 1 + QT - 1) / QT;      // wavenumber pairs (k, M - k) per thread
+  // wavenumber pairs (k, M - k) of a line, 0 <= k <= M/2, and per thread; for
+  // the DCT-IV types the pairs (k, M - 1 - k).  The contiguous layout deals
+  // out the pairs of all lines over the block (line-major), so that the lanes
+  // of a wave run along a line however few threads a line has.
+  static constexpr int NP = M / 2 + 1, NQ = (M + 1) / 2;
+  static constexpr int per_thread(int pairs, int layout) {
+    return layout == 0 ? (pairs + QT - 1) / QT : (pairs * NL + NT - 1) / NT;
+  }
   static constexpr int SPLIT = M / 2 + 1;
   static constexpr size_t lds_bytes(int pipe) {
     return (size_t)TILE * sizeof(T) +
@@ -269,6 +276,7 @@ void r2r_line_kernel(R2RFastArgs<T> A) {
   constexpr int M = L::M, N = L::N, NL = L::NL, NT = L::NT, QT = L::QT, NLP = L::NLP;
   constexpr int H = M / 2;
   using T2 = T __attribute__((ext_vector_type(2)));
+  using T2u = T __attribute__((ext_vector_type(2), aligned(sizeof(T))));   // at any element
   if (A.skip && A.skip[0] != 0.0) return;
   __shared__ __align__(16) unsigned char raw[L::lds_bytes(PIPE)];
   const lptr<T> tile_lds = as_lds(reinterpret_cast<T*>(raw));
@@ -328,35 +336,66 @@ void r2r_line_kernel(R2RFastArgs<T> A) {
 
   // registers of the next tile: PIPE_INV holds the four rows of each of the
   // thread's wavenumber pairs, the others the thread's points in order
-  constexpr int NBUF = PIPE == PIPE_INV ? 4 * L::SP : LAYOUT == 0 ? L::EP : 2 * L::EC;
+  constexpr int SP = L::per_thread(L::NP, LAYOUT), SQ = L::per_thread(L::NQ, LAYOUT);
+  constexpr int NBUF = PIPE == PIPE_INV ? 4 * SP : LAYOUT == 0 ? L::EP : 2 * L::EC;
   T buf[NBUF];
+  // pair s of the thread: its line of the tile and k (past the end: the last
+  // pair again)
+  struct Pair {
+    int ln, k;
+  };
+  auto pair_at = [&](int s, int pairs, int l, int q, int tid) -> Pair {
+    if constexpr (LAYOUT == 0) {
+      const int k = q + s * QT;
+      return Pair{l, pairs % QT == 0 ? k : min(k, pairs - 1)};
+    } else {
+      int e = tid + s * NT;
+      if ((pairs * NL) % NT != 0) e = min(e, pairs * NL - 1);
+      const int ln = e / pairs;
+      return Pair{ln, e - ln * pairs};
+    }
+  };
 
   auto fetch = [&](int tile, int l, int q, int tid) {
     const Tile t = tile_at(tile);
     const gptr<const T> tb = src + t.base;
     if constexpr (PIPE == PIPE_INV) {
-      const int ln = LAYOUT == 0 ? l : tid / QT, qq = LAYOUT == 0 ? q : tid % QT;
-      const unsigned lo = line_off(t, ln);
       // rows of wavenumber k and M - k (combine below); those that k = 0
-      // does not have repeat row 0
+      // does not have repeat another
       auto rows = [&](auto f) {
 #pragma unroll
-        for (int s = 0; s < L::SP; ++s) {
-          const int k = min(qq + s * QT, H);
+        for (int s = 0; s < SP; ++s) {
+          const Pair pr = pair_at(s, L::NP, l, q, tid);
+          const unsigned lo = line_off(t, pr.ln);
           int r[4];
-          f(k, r);
+          f(pr.k, r);
 #pragma unroll
           for (int a = 0; a < 4; ++a) buf[4 * s + a] = tb[at(lo, r[a])];
         }
       };
-      if (kind == K_P)
-        rows([&](int k, int (&r)[4]) {
-          r[0] = max(2 * k - 1, 0);
-          r[1] = 2 * k;
-          r[2] = N - 1 - 2 * k;
-          r[3] = min(N - 2 * k, N - 1);
-        });
-      else if (kind == K_NN)
+      if (kind == K_P) {
+        if constexpr (LAYOUT == 0) {
+          rows([&](int k, int (&r)[4]) {
+            r[0] = max(2 * k - 1, 0);
+            r[1] = 2 * k;
+            r[2] = N - 1 - 2 * k;
+            r[3] = min(N - 2 * k, N - 1);
+          });
+        } else {   // two adjacent points per load
+#pragma unroll
+          for (int s = 0; s < SP; ++s) {
+            const Pair pr = pair_at(s, L::NP, l, q, tid);
+            const int k = pr.k;
+            const gptr<const T> row = tb + line_off(t, pr.ln);
+            const T2u lo = *reinterpret_cast<const gptr<const T2u>>(row + max(2 * k - 1, 0));
+            const T2u hi = *reinterpret_cast<const gptr<const T2u>>(row + min(N - 1 - 2 * k, N - 2));
+            buf[4 * s] = lo.x;
+            buf[4 * s + 1] = lo.y;
+            buf[4 * s + 2] = k == 0 ? hi.y : hi.x;
+            buf[4 * s + 3] = hi.y;
+          }
+        }
+      } else if (kind == K_NN)
         rows([&](int k, int (&r)[4]) {
           r[0] = k;
           r[1] = min(N - k, N - 1);
@@ -392,9 +431,8 @@ void r2r_line_kernel(R2RFastArgs<T> A) {
 
   auto place = [&](int l, int q, int tid) {
     if constexpr (PIPE == PIPE_INV) {
-      const int ln = LAYOUT == 0 ? l : tid / QT, qq = LAYOUT == 0 ? q : tid % QT;
       // Z'_k = (X_k + conj X_{M-k}) + i (X_k - conj X_{M-k}) e^{2 pi i k/n}
-      auto put = [&](int k, cplx<T> xk, cplx<T> xj) {
+      auto put = [&](int ln, int k, cplx<T> xk, cplx<T> xj) {
         const cplx<T> sk = ldc(twa, k);
         const cplx<T> s1 = cadd(xk, cconj(xj)), d = csub(xk, cconj(xj));
         const cplx<T> d1 = cmul_fixed(d, cconj(sk));
@@ -409,8 +447,9 @@ void r2r_line_kernel(R2RFastArgs<T> A) {
         }
       };
 #pragma unroll
-      for (int s = 0; s < L::SP; ++s) {
-        const int k = min(qq + s * QT, H);
+      for (int s = 0; s < SP; ++s) {
+        const Pair pr = pair_at(s, L::NP, l, q, tid);
+        const int k = pr.k;
         cplx<T> xk, xj;
         if (kind == K_P) {
           xk = {buf[4 * s], k == 0 ? (T)0 : -buf[4 * s + 1]};
@@ -419,7 +458,7 @@ void r2r_line_kernel(R2RFastArgs<T> A) {
           xk = cmul_fixed(cconj(ldc(twb, k)), cplx<T>{(T)0.5 * buf[4 * s], k == 0 ? (T)0 : (T)-0.5 * buf[4 * s + 1]});
           xj = cmul_fixed(cconj(ldc(twb, M - k)), cplx<T>{(T)0.5 * buf[4 * s + 2], (T)-0.5 * buf[4 * s + 3]});
         }
-        put(k, xk, xj);
+        put(pr.ln, k, xk, xj);
       }
     } else if constexpr (LAYOUT == 0) {
 #pragma unroll
@@ -455,11 +494,11 @@ void r2r_line_kernel(R2RFastArgs<T> A) {
     const gptr<O> tb = as_global(field) + t.base;
     const T scale = A.scale;
     if constexpr (PIPE == PIPE_FWD) {
-      const int ln = LAYOUT == 0 ? l : tid / QT, qq = LAYOUT == 0 ? q : tid % QT;
-      const unsigned lo = line_off(t, ln);
 #pragma unroll
-      for (int s = 0; s < L::SP; ++s) {
-        const int k = min(qq + s * QT, H);
+      for (int s = 0; s < SP; ++s) {
+        const Pair pr = pair_at(s, L::NP, l, q, tid);
+        const int ln = pr.ln, k = pr.k;
+        const unsigned lo = line_off(t, ln);
         const int j = M - k, kc = k == 0 ? 0 : j;
         const cplx<T> z = {tile_lds[(2 * k) * NLP + ln], tile_lds[(2 * k + 1) * NLP + ln]};
         const cplx<T> zc = {tile_lds[(2 * kc) * NLP + ln], -tile_lds[(2 * kc + 1) * NLP + ln]};
@@ -501,20 +540,25 @@ void r2r_line_kernel(R2RFastArgs<T> A) {
             for (int a = 0; a < 4; ++a) r[a] = N - 1 - r[a];
           }
         }
+        if (LAYOUT == 1 && kind == K_P && k > 0) {   // adjacent points 2k-1, 2k and 2j-1, 2j
+          using O2u = O __attribute__((ext_vector_type(2), aligned(sizeof(O))));
+          *reinterpret_cast<gptr<O2u>>(tb + lo + r[0]) = O2u{(O)(v[0] * scale), (O)(v[1] * scale)};
+          *reinterpret_cast<gptr<O2u>>(tb + lo + r[2]) = O2u{(O)(v[2] * scale), (O)(v[3] * scale)};
+        } else {
 #pragma unroll
-        for (int a = 0; a < 4; ++a) tb[at(lo, r[a])] = (O)(v[a] * scale);
+          for (int a = 0; a < 4; ++a) tb[at(lo, r[a])] = (O)(v[a] * scale);
+        }
       }
     } else if constexpr (PIPE == PIPE_IV) {
-      const int ln = LAYOUT == 0 ? l : tid / QT, qq = LAYOUT == 0 ? q : tid % QT;
-      const unsigned lo = line_off(t, ln);
       const T so = kind == K_ND ? (T)-2 : (T)2;   // the DST-IV negates odd points
       // V_k = Z_k times the post-twiddle: point 2k = 2 Re V_k, point n-1-2k =
       // -2 Im V_k; k and M-1-k together give the adjacent points 2k, 2k+1
       // and n-2-2k, n-1-2k
-      constexpr int HP = (M + 1) / 2, SV = (HP + QT - 1) / QT;
 #pragma unroll
-      for (int s = 0; s < SV; ++s) {
-        const int k = HP % QT == 0 ? qq + s * QT : min(qq + s * QT, HP - 1);
+      for (int s = 0; s < SQ; ++s) {
+        const Pair pr = pair_at(s, L::NQ, l, q, tid);
+        const int ln = pr.ln, k = pr.k;
+        const unsigned lo = line_off(t, ln);
         const int j = M - 1 - k;
         const cplx<T> V = cmul(cplx<T>{tile_lds[(2 * k) * NLP + ln], tile_lds[(2 * k + 1) * NLP + ln]},
                                ldc(twb, k));
@@ -573,25 +617,32 @@ void r2r_line_kernel(R2RFastArgs<T> A) {
   // the next tile is placed at the bottom of the loop, after the current
   // tile's stores, so that the waits for its loads count those stores
   for (int tile = tr.first; tile < tr.end; tile += tr.step) {
-    // thread index opaque per tile: addresses are recomputed in each step
-    // instead of being held (or spilled) across the loop
+    // thread index opaque per tile, and with 128 registers per step:
+    // addresses are recomputed instead of being held (or spilled) across the
+    // loop.  With 256 registers the steps are faster with them held (n = 640
+    // along x 5.24 against 4.99 TB/s).
     int tid = tid0;
     asm volatile("" : "+v"(tid));
-    const int l = tid % NL, q = tid / NL;
+    auto step = [&] {
+      if constexpr (WAVES > 2) asm volatile("" : "+v"(tid));
+    };
     lds_barrier();
     const bool more = tile + tr.step < tr.end;
-    if (more) fetch(tile + tr.step, l, q, tid);
-    line_passes<T, C, PIPE != PIPE_INV, PIPE == PIPE_IV>(tile_lds, twf, twa, l, q);
+    if (more) fetch(tile + tr.step, tid % NL, tid / NL, tid);
+    step();
+    line_passes<T, C, PIPE != PIPE_INV, PIPE == PIPE_IV>(tile_lds, twf, twa, tid % NL, tid / NL);
+    step();
     bool widened = false;
     if constexpr (sizeof(T) == 4 && PIPE != PIPE_FWD) {
       if (A.out64) {   // last pass of an FP32 solve: the widened result
-        store(A.out64, tile, l, q, tid);
+        store(A.out64, tile, tid % NL, tid / NL, tid);
         widened = true;
       }
     }
-    if (!widened) store(A.data, tile, l, q, tid);
+    if (!widened) store(A.data, tile, tid % NL, tid / NL, tid);
     lds_barrier();
-    if (more) place(l, q, tid);
+    step();
+    if (more) place(tid % NL, tid / NL, tid);
   }
 }
 

@@ -8,26 +8,22 @@
 
 namespace poisson_dev {
 
-template <typename T, int M>
-static hipError_t line_launch(const R2RFastArgs<T>& a, hipStream_t stream) {
-  constexpr LineShape S = line_shape(sizeof(T), M);
-  using C = LineCfg<M, S.nl, S.nt>;
-  using L = LineLayout<T, C>;
-  // waves per SIMD that the LDS allows
-  constexpr int W = 80 * 1024 / L::lds_bytes(PIPE_IV) > 0 ? 4 : 2;
-  void (*k)(R2RFastArgs<T>) = nullptr;
-  const int pipe = a.kind >= K_ND ? PIPE_IV : a.inverse ? PIPE_INV : PIPE_FWD;
-  switch (pipe * 2 + a.g.layout) {
-    case 0: k = r2r_line_kernel<T, C, PIPE_FWD, 0, W>; break;
-    case 1: k = r2r_line_kernel<T, C, PIPE_FWD, 1, W>; break;
-    case 2: k = r2r_line_kernel<T, C, PIPE_INV, 0, W>; break;
-    case 3: k = r2r_line_kernel<T, C, PIPE_INV, 1, W>; break;
-    case 4: k = r2r_line_kernel<T, C, PIPE_IV, 0, W>; break;
-    default: k = r2r_line_kernel<T, C, PIPE_IV, 1, W>; break;
-  }
+template <typename T, int M, int LAYOUT>
+static hipError_t line_launch_layout(const R2RFastArgs<T>& a, hipStream_t stream) {
+  constexpr LineShape S = line_shape(sizeof(T), M, LAYOUT);
+  // FP64 values of a radix-20 or radix-25 butterfly take more than 128 registers
+  using C = LineCfg<M, S.nl, S.nt, sizeof(T) == 8 && S.waves == 4 ? 18 : 25>;
+  void (*k)(R2RFastArgs<T>) = a.kind >= K_ND ? r2r_line_kernel<T, C, PIPE_IV, LAYOUT, S.waves>
+                              : a.inverse    ? r2r_line_kernel<T, C, PIPE_INV, LAYOUT, S.waves>
+                                             : r2r_line_kernel<T, C, PIPE_FWD, LAYOUT, S.waves>;
   const int blocks = async_resident_blocks(reinterpret_cast<const void*>(k), a.g.ntiles, S.nt);
   hipLaunchKernelGGL(k, dim3(blocks), dim3(S.nt), 0, stream, a);
   return hipGetLastError();
+}
+
+template <typename T, int M>
+static hipError_t line_launch(const R2RFastArgs<T>& a, hipStream_t stream) {
+  return a.g.layout == 0 ? line_launch_layout<T, M, 0>(a, stream) : line_launch_layout<T, M, 1>(a, stream);
 }
 
 #define POISSON_LINE_DEFINE(M_)                                                    \

@@ -1,5 +1,5 @@
 """The per-length transform kernels (every n = 2M, 12 <= M <= 512, M =
-2^a 3^b 5^c): all five transform types, both directions, on the contiguous
+2^a 3^b 5^c, but n = 512): all five transform types, both directions, on the contiguous
 axis and on both strided axes, with ragged tiles (odd x extents, fewer lines
 than a tile, a last tile that is nearly empty) and with the grid capped so
 that blocks loop over tiles.  Against the Table 2 sums (<= 1e-13 relative L2,
@@ -15,9 +15,7 @@ from paper_1802_10323_amd import inputs
 pytestmark = pytest.mark.gpu
 
 KINDS = ("P", "NN", "DD", "ND", "DN")
-# the other lengths have kernels of their own (variants 0-7)
-OWN = (32, 64, 96, 128, 144, 160, 192, 256, 288, 320, 384, 512)
-LENGTHS = [n for n in inputs.smooth_sizes(24, 1024) if n not in OWN]
+LENGTHS = [n for n in inputs.smooth_sizes(24, 1024) if n != 512]
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -71,7 +69,8 @@ def test_line_transform(n, monkeypatch):
             assert rel_l2(back, gen) <= 2e-13, (axis, kind, shape)
 
 
-@pytest.mark.parametrize("nx,ny", [(24, 1000), (50, 810), (270, 54), (300, 250), (600, 100), (1024, 90)])
+@pytest.mark.parametrize("nx,ny", [(24, 1000), (50, 810), (270, 54), (300, 250), (600, 100), (1024, 90),
+                                   (96, 128), (288, 384)])
 @pytest.mark.parametrize("bx", KINDS)
 def test_line_transform_fp32(nx, ny, bx, monkeypatch):
     """One FP32 solve (forward and backward along both axes; the last backward
