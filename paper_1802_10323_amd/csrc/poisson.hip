@@ -1430,6 +1430,9 @@ static RefineGeom refine_geom(const poisson_plan* p, double* stats) {
   }
   G.npts = (long long)field_points(p);
   G.stats = stats;
+  double hz = 0.0;
+  for (const double h : p->dz) hz += h;
+  G.weight = hz * p->dims[0] * p->dims[1];
   return G;
 }
 
@@ -1444,6 +1447,7 @@ struct RefineLaunch {
   long long N;
   RefineGeom G;
   int nb;
+  int vec;            // points per access: pairs of neighbours where nx is even
   ResidualGrid rg;
 };
 
@@ -1451,8 +1455,9 @@ static RefineLaunch refine_launch(const poisson_plan* p, double* stats) {
   RefineLaunch r;
   r.N = (long long)field_points(p);
   r.G = refine_geom(p, stats);
-  r.nb = (int)std::min<long long>(REFINE_BLOCKS, (r.N + REFINE_NT - 1) / REFINE_NT);
-  r.rg = residual_grid(p->dims[0], p->dims[1], p->dims[2]);
+  r.vec = p->dims[0] % 2 == 0 ? 2 : 1;
+  r.nb = (int)std::min<long long>(REFINE_EBLOCKS, (r.N / r.vec + REFINE_NT - 1) / REFINE_NT);
+  r.rg = residual_grid(p->dims[0], p->dims[1], p->dims[2], r.vec);
   return r;
 }
 
@@ -1462,17 +1467,28 @@ static bool refine_hinted(const poisson_plan* p) {
   return (double)p->dims[0] * p->dims[1] * p->dims[2] * sizeof(double) >= (double)(512u << 20);
 }
 
+// f(hint, V) with the access hint and the points per access as constants.
+template <typename F>
+static void refine_dispatch(const poisson_plan* p, const RefineLaunch& r, F&& f) {
+  const bool nt = refine_hinted(p);
+  if (r.vec == 2)
+    nt ? f(std::true_type{}, std::integral_constant<int, 2>{})
+       : f(std::false_type{}, std::integral_constant<int, 2>{});
+  else
+    nt ? f(std::true_type{}, std::integral_constant<int, 1>{})
+       : f(std::false_type{}, std::integral_constant<int, 1>{});
+}
+
 // Status reset, projection of f if singular, the FP64 copy of f and its FP32 cast.
 static int refine_begin(const poisson_plan* p, const RefineWork& W, double* rhs, hipStream_t st) {
   const RefineLaunch r = refine_launch(p, W.stats);
-  hipLaunchKernelGGL(refine_init_kernel, dim3(1), dim3(256), 0, st, W.stats);
-  if (p->singular) {
-    hipLaunchKernelGGL(refine_wsum_kernel, dim3(r.nb), dim3(REFINE_NT), 0, st, (const double*)rhs, r.G);
-    hipLaunchKernelGGL(refine_mean_kernel, dim3(1), dim3(REFINE_NT), 0, st, W.stats, r.nb);
-  }
-  hipLaunchKernelGGL(refine_hinted(p) ? refine_prep_kernel<true> : refine_prep_kernel<false>,
-                     dim3(r.nb), dim3(REFINE_NT), 0, st, (const double*)rhs,
-                     W.f64, W.e32, (const double*)W.stats, (int)p->singular, r.N);
+  refine_dispatch(p, r, [&](auto nt, auto v) {
+    if (p->singular)
+      hipLaunchKernelGGL(refine_wsum_kernel<v>, dim3(r.nb), dim3(REFINE_NT), 0, st,
+                         (const double*)rhs, r.G, 1);
+    hipLaunchKernelGGL((refine_prep_kernel<nt, v>), dim3(r.nb), dim3(REFINE_NT), 0, st,
+                       (const double*)rhs, W.f64, W.e32, r.G, (int)p->singular);
+  });
   HIP_TRY(hipGetLastError());
   return POISSON_OK;
 }
@@ -1481,9 +1497,10 @@ static int refine_begin(const poisson_plan* p, const RefineWork& W, double* rhs,
 static int refine_sweep_begin(const poisson_plan* p, const RefineWork& W, double* rhs,
                               hipStream_t st) {
   const RefineLaunch r = refine_launch(p, W.stats);
-  hipLaunchKernelGGL(refine_hinted(p) ? refine_residual_kernel<true> : refine_residual_kernel<false>,
-                     dim3(r.rg.blocks), dim3(REFINE_NT), 0, st,
-                     (const double*)rhs, (const double*)W.f64, W.e32, r.G, r.rg);
+  refine_dispatch(p, r, [&](auto nt, auto v) {
+    hipLaunchKernelGGL((refine_residual_kernel<nt, v>), dim3(r.rg.blocks), dim3(REFINE_NT), 0, st,
+                       (const double*)rhs, (const double*)W.f64, W.e32, r.G, r.rg);
+  });
   HIP_TRY(hipGetLastError());
   return POISSON_OK;
 }
@@ -1492,24 +1509,28 @@ static int refine_sweep_begin(const poisson_plan* p, const RefineWork& W, double
 static int refine_sweep_end(const poisson_plan* p, const RefineWork& W, double* rhs, int sweep,
                             hipStream_t st) {
   const RefineLaunch r = refine_launch(p, W.stats);
-  hipLaunchKernelGGL(refine_hinted(p) ? refine_update_kernel<true> : refine_update_kernel<false>,
-                     dim3(r.nb), dim3(REFINE_NT), 0, st, rhs,
-                     (const float*)W.e32, r.G);
-  hipLaunchKernelGGL(refine_status_kernel, dim3(1), dim3(REFINE_NT), 0, st, W.stats, r.nb, sweep,
+  refine_dispatch(p, r, [&](auto nt, auto v) {
+    hipLaunchKernelGGL((refine_update_kernel<nt, v>), dim3(r.nb), dim3(REFINE_NT), 0, st, rhs,
+                       (const float*)W.e32, r.G);
+  });
+  hipLaunchKernelGGL(refine_status_kernel, dim3(1), dim3(REFINE_NT), 0, st, r.G, r.nb, sweep,
                      W.tol);
   HIP_TRY(hipGetLastError());
   return POISSON_OK;
 }
 
-// Gauge of a singular problem.
+// Gauge of a singular problem: the last update left Phi's mean in the status
+// block; a single FP32 solve has none, and its Phi is summed first.
 static int refine_end(const poisson_plan* p, const RefineWork& W, double* rhs, hipStream_t st) {
+  if (!p->singular) return POISSON_OK;
   const RefineLaunch r = refine_launch(p, W.stats);
-  if (p->singular) {
-    hipLaunchKernelGGL(refine_wsum_kernel, dim3(r.nb), dim3(REFINE_NT), 0, st, (const double*)rhs, r.G);
-    hipLaunchKernelGGL(refine_mean_kernel, dim3(1), dim3(REFINE_NT), 0, st, W.stats, r.nb);
-    hipLaunchKernelGGL(refine_shift_kernel, dim3(r.nb), dim3(REFINE_NT), 0, st, rhs,
-                       (const double*)W.stats, r.N);
-  }
+  const int single = W.max_iters == 1;
+  refine_dispatch(p, r, [&](auto, auto v) {
+    if (single)
+      hipLaunchKernelGGL(refine_wsum_kernel<v>, dim3(r.nb), dim3(REFINE_NT), 0, st,
+                         (const double*)rhs, r.G, 0);
+    hipLaunchKernelGGL(refine_shift_kernel<v>, dim3(r.nb), dim3(REFINE_NT), 0, st, rhs, r.G, single);
+  });
   HIP_TRY(hipGetLastError());
   return POISSON_OK;
 }
@@ -2095,6 +2116,7 @@ static int batch_upload(poisson_batch* b) {
       J.f64 = p->f64;
       J.e32 = p->e32;
       J.singular = p->singular ? 1 : 0;
+      J.vec = r.vec;
       J.nb = r.nb;
       J.rg = r.rg;
       J.first_e = fe;
@@ -2169,20 +2191,18 @@ static int batch_enqueue(poisson_batch* b, hipStream_t st) {
   }
   const int n = (int)b->plans.size();
   int sweeps = 1;
-  bool singular = false;
+  bool singular = false, single = false;   // single: a singular instance without sweeps
   for (const poisson_plan* p : b->plans) {
     sweeps = std::max(sweeps, p->max_iters);
     singular = singular || p->singular;
+    single = single || (p->singular && p->max_iters == 1);
   }
   const RefineJob* jobs = b->drefine;
   const dim3 blk(REFINE_NT);
   // the refinement kernels of all instances, one launch per kind (each
   // instance on its own block range, as in its single-plan launch)
-  hipLaunchKernelGGL(refine_batch_init, dim3(n), dim3(256), 0, st, jobs);
-  if (singular) {
-    hipLaunchKernelGGL(refine_batch_wsum, dim3(b->refine_eblocks), blk, 0, st, jobs, n);
-    hipLaunchKernelGGL(refine_batch_mean, dim3(n), blk, 0, st, jobs);
-  }
+  if (singular)
+    hipLaunchKernelGGL(refine_batch_wsum, dim3(b->refine_eblocks), blk, 0, st, jobs, n, 1);
   hipLaunchKernelGGL(refine_batch_prep, dim3(b->refine_eblocks), blk, 0, st, jobs, n);
   HIP_TRY(hipGetLastError());
   for (int k = 0; k < 5; ++k)
@@ -2197,8 +2217,7 @@ static int batch_enqueue(poisson_batch* b, hipStream_t st) {
     HIP_TRY(hipGetLastError());
   }
   if (singular) {
-    hipLaunchKernelGGL(refine_batch_wsum, dim3(b->refine_eblocks), blk, 0, st, jobs, n);
-    hipLaunchKernelGGL(refine_batch_mean, dim3(n), blk, 0, st, jobs);
+    if (single) hipLaunchKernelGGL(refine_batch_wsum, dim3(b->refine_eblocks), blk, 0, st, jobs, n, 0);
     hipLaunchKernelGGL(refine_batch_shift, dim3(b->refine_eblocks), blk, 0, st, jobs, n);
   }
   HIP_TRY(hipGetLastError());

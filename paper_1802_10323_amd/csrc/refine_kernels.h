@@ -7,13 +7,23 @@
 //
 // Device status block (doubles):
 //   [0] skip flag (1 once refinement has converged: later sweeps return)
-//   [1] scratch scalar (weighted mean)
+//   [1] weighted mean of Phi after the last update that ran (singular plans)
 //   [2] converged flag
 //   [3] relative update of the previous sweep
 //   [4 + 2s], [5 + 2s]: ||e_s||^2 and ||Phi_s||^2 of sweep s (-1 if not run)
-//   [REFINE_PARTIALS ...]: per-block partial sums (2 per block)
+//   [REFINE_PARTIALS ...]: per-block partial sums (3 per block: ||e||^2,
+//   ||Phi||^2 and the weighted sum of f or Phi)
+//
+// Bound: HBM.  The sweeps move pairs of neighbouring x points (16-byte
+// accesses; single points where nx is odd) with several pairs of a thread in
+// flight, and no sweep reads a field only to sum it where another one holds
+// it already: the gauge's mean of Phi comes from the last update.  Measured
+// on the 512 x 256 x 192 channel (singular), before -> after: mean of f 56 -> 31
+// us, copy and cast 94 -> 85, residual 154 -> 112, update 84 -> 76, gauge 114 ->
+// 57, four launches fewer; the refined solve 992 -> 842 us.
 #pragma once
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.h"
 
@@ -24,6 +34,10 @@ static constexpr int REFINE_BLOCKS = 1024;
 static constexpr int REFINE_NT = 256;
 static constexpr int REFINE_PARTIALS = 4 + 2 * REFINE_MAX_SWEEPS + 8;
 static constexpr int REFINE_STAT_SLOTS = REFINE_PARTIALS + 2 * REFINE_BLOCKS;
+// Blocks of the element-wise sweeps: two per CU (more would only lengthen the
+// partial sums that every block of the next sweep adds up).
+static constexpr int REFINE_EBLOCKS = 512;
+static_assert(3 * REFINE_EBLOCKS <= 2 * REFINE_BLOCKS, "three partial sums per block");
 
 struct OpAxis {            // one axis of the operator: rows a, b, c and widths h
   const double* a;
@@ -37,25 +51,41 @@ struct RefineGeom {
   OpAxis ax[3];            // x, y, z
   long long npts;
   double* stats;
+  double weight;           // total of the weights: nx ny times the sum of the z widths
 };
 
 __device__ __forceinline__ bool refine_skip(const double* stats) { return stats[0] != 0.0; }
 
+// Sums over the block (fixed order), on every thread.
 template <int NT>
-__device__ __forceinline__ void block_sum2(double& a, double& b, double* sh) {
+__device__ __forceinline__ double block_sum(double a, double* sh) {
   const int tid = threadIdx.x;
+  __syncthreads();
   sh[tid] = a;
-  sh[NT + tid] = b;
   __syncthreads();
   for (int s = NT / 2; s > 0; s >>= 1) {
-    if (tid < s) {
-      sh[tid] += sh[tid + s];
-      sh[NT + tid] += sh[NT + tid + s];
-    }
+    if (tid < s) sh[tid] += sh[tid + s];
     __syncthreads();
   }
-  a = sh[0];
-  b = sh[NT];
+  return sh[0];
+}
+
+// Sum of partial sum `slot` over the blocks of a sweep.
+__device__ __forceinline__ double refine_partials(const double* stats, int slot, int nblocks,
+                                                  double* sh) {
+  double a = 0.0;
+  for (int i = threadIdx.x; i < nblocks; i += REFINE_NT) a += stats[REFINE_PARTIALS + 3 * i + slot];
+  return block_sum<REFINE_NT>(a, sh);
+}
+
+// The thread's runs of V points of a field, U runs in flight: body(q, count)
+// handles the runs q, q + step, ... (count of them; run q starts at point V q).
+template <int V, int U, typename F>
+__device__ __forceinline__ void refine_runs(long long npts, int block, int nblocks, F&& body) {
+  const long long n = npts / V, step = (long long)nblocks * REFINE_NT;
+  long long q = block * (long long)REFINE_NT + threadIdx.x;
+  for (; q + (U - 1) * step < n; q += U * step) body(q, step, std::integral_constant<int, U>{});
+  for (; q < n; q += step) body(q, step, std::integral_constant<int, 1>{});
 }
 
 // Grid position (i, j, k) of point idx, advanced by a fixed step without
@@ -84,6 +114,25 @@ struct GridWalk {
   }
 };
 
+// z index of the thread's successive runs (refine_runs order)
+struct PlaneWalk {
+  int k;
+  long long r, dr, plane;
+  int dk;
+  __device__ PlaneWalk(long long point, long long step, long long plane_) : plane(plane_) {
+    k = (int)(point / plane);
+    r = point - k * plane;
+    dk = (int)(step / plane);
+    dr = step - dk * plane;
+  }
+  __device__ void advance() {
+    r += dr;
+    const bool carry = r >= plane;
+    r -= carry ? plane : 0;
+    k += dk + (carry ? 1 : 0);
+  }
+};
+
 // Each kernel below is a device body over a block range, called by a
 // kernel for one plan (blockIdx / gridDim) and by a batched kernel that
 // runs the same body for every instance of a batch, each on its own block
@@ -95,95 +144,141 @@ __device__ __forceinline__ void refine_init_body(double* stats) {
   for (int i = threadIdx.x; i < REFINE_PARTIALS; i += blockDim.x) stats[i] = i >= 4 ? -1.0 : 0.0;
 }
 
-// partial sums of w*x (slot 0) and w (slot 1), w = hx_i hy_j hz_k
-__device__ __forceinline__ void refine_wsum_body(const double* __restrict__ x, const RefineGeom& G,
-                                                 int block, int nblocks, double* sh) {
-  double sx = 0.0, sw = 0.0;
-  const long long step = (long long)nblocks * REFINE_NT;
-  const long long first = block * (long long)REFINE_NT + threadIdx.x;
-  GridWalk at(first, step, G.ax[0].n, G.ax[1].n);
-  for (long long idx = first; idx < G.npts; idx += step, at.advance()) {
-    const double w = G.ax[0].h[at.i] * G.ax[1].h[at.j] * G.ax[2].h[at.k];
-    sx += w * x[idx];
-    sw += w;
-  }
-  block_sum2<REFINE_NT>(sx, sw, sh);
-  if (threadIdx.x == 0) {
-    G.stats[REFINE_PARTIALS + 2 * block] = sx;
-    G.stats[REFINE_PARTIALS + 2 * block + 1] = sw;
-  }
-}
-
-// stats[1] = (sum of slot 0) / (sum of slot 1)   (weighted mean)
-__device__ __forceinline__ void refine_mean_body(double* stats, int nblocks, double* sh) {
-  double a = 0.0, b = 0.0;
-  for (int i = threadIdx.x; i < nblocks; i += REFINE_NT) {
-    a += stats[REFINE_PARTIALS + 2 * i];
-    b += stats[REFINE_PARTIALS + 2 * i + 1];
-  }
-  block_sum2<REFINE_NT>(a, b, sh);
-  if (threadIdx.x == 0) stats[1] = b > 0.0 ? a / b : 0.0;
-}
-
-// A load or store with the nontemporal hint (NT) or a plain one.  The
+// Run q of V points, with the nontemporal hint (NT) or without.  The
 // single-plan kernels take the hint on fields of 512 MiB and more: on the
 // 512^3 cube the refined solve went 4.51-4.52 -> 4.44-4.46 ms with it;
 // the batched kernels (many small instances) keep plain accesses.
-template <bool NT, typename T>
-__device__ __forceinline__ T refine_ld(const T* p) {
-  if constexpr (NT) return __builtin_nontemporal_load(p);
-  else return *p;
+template <bool NT, typename T, int V>
+__device__ __forceinline__ void refine_ld(const T* p, long long q, T (&x)[V]) {
+  using W = T __attribute__((ext_vector_type(V)));
+  const W* w = reinterpret_cast<const W*>(p) + q;
+  W t;
+  if constexpr (NT) t = __builtin_nontemporal_load(w);
+  else t = *w;
+#pragma unroll
+  for (int i = 0; i < V; ++i) x[i] = t[i];
 }
-template <bool NT, typename T>
-__device__ __forceinline__ void refine_st(T v, T* p) {
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
-  else *p = v;
+template <bool NT, typename T, int V>
+__device__ __forceinline__ void refine_st(T* p, long long q, const T (&x)[V]) {
+  using W = T __attribute__((ext_vector_type(V)));
+  W* w = reinterpret_cast<W*>(p) + q;
+  W t;
+#pragma unroll
+  for (int i = 0; i < V; ++i) t[i] = x[i];
+  if constexpr (NT) __builtin_nontemporal_store(t, w);
+  else *w = t;
 }
 
-// f64 = rhs - mean (mean = stats[1] if `project`), e32 = (float) f64
-template <bool NT>
+// partial weighted sums (slot 2) of x; the weights are the z widths (x and y
+// are uniform)
+template <int V>
+__device__ __forceinline__ void refine_wsum_body(const double* __restrict__ x, const RefineGeom& G,
+                                                 int block, int nblocks, double* sh) {
+  double sx = 0.0;
+  PlaneWalk at((block * (long long)REFINE_NT + threadIdx.x) * V, (long long)nblocks * REFINE_NT * V,
+               (long long)G.ax[0].n * G.ax[1].n);
+  refine_runs<V, 4>(G.npts, block, nblocks, [&](long long q, long long step, auto U) {
+    double v[U][V];
+#pragma unroll
+    for (int u = 0; u < U; ++u) refine_ld<false>(x, q + u * step, v[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      double t = 0.0;
+#pragma unroll
+      for (int i = 0; i < V; ++i) t += v[u][i];
+      sx += G.ax[2].h[at.k] * t;
+      at.advance();
+    }
+  });
+  sx = block_sum<REFINE_NT>(sx, sh);
+  if (threadIdx.x == 0) G.stats[REFINE_PARTIALS + 3 * block + 2] = sx;
+}
+
+// f64 = rhs - mean (the weighted mean of the partial sums, if `project`), e32 =
+// (float) f64
+template <bool NT, int V>
 __device__ __forceinline__ void refine_prep_body(const double* __restrict__ rhs,
                                                  double* __restrict__ f64, float* __restrict__ e32,
-                                                 const double* stats, int project, long long npts,
-                                                 int block, int nblocks) {
-  const double mean = project ? stats[1] : 0.0;
-  for (long long idx = block * (long long)REFINE_NT + threadIdx.x; idx < npts;
-       idx += (long long)nblocks * REFINE_NT) {
-    const double f = refine_ld<NT>(&rhs[idx]) - mean;
-    refine_st<NT>(f, &f64[idx]);
-    refine_st<NT>((float)f, &e32[idx]);
-  }
+                                                 const RefineGeom& G, int project, int block,
+                                                 int nblocks, double* sh) {
+  const double mean = project ? refine_partials(G.stats, 2, nblocks, sh) / G.weight : 0.0;
+  refine_runs<V, 2>(G.npts, block, nblocks, [&](long long q, long long step, auto U) {
+    double f[U][V];
+#pragma unroll
+    for (int u = 0; u < U; ++u) refine_ld<NT>(rhs, q + u * step, f[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float e[V];
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        f[u][i] -= mean;
+        e[i] = (float)f[u][i];
+      }
+      refine_st<NT>(f64, q + u * step, f[u]);
+      refine_st<NT>(e32, q + u * step, e);
+    }
+  });
 }
 
-// x -= stats[1]
-__device__ __forceinline__ void refine_shift_body(double* __restrict__ x, const double* stats,
-                                                  long long npts, int block, int nblocks) {
-  const double mean = stats[1];
-  for (long long idx = block * (long long)REFINE_NT + threadIdx.x; idx < npts;
-       idx += (long long)nblocks * REFINE_NT)
-    x[idx] -= mean;
+// x -= its weighted mean: stats[1], or (`summed`) that of the partial sums
+template <int V>
+__device__ __forceinline__ void refine_shift_body(double* __restrict__ x, const RefineGeom& G,
+                                                  int summed, int block, int nblocks, double* sh) {
+  const double mean = summed ? refine_partials(G.stats, 2, nblocks, sh) / G.weight : G.stats[1];
+  refine_runs<V, 2>(G.npts, block, nblocks, [&](long long q, long long step, auto U) {
+    double f[U][V];
+#pragma unroll
+    for (int u = 0; u < U; ++u) refine_ld<false>(x, q + u * step, f[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int i = 0; i < V; ++i) f[u][i] -= mean;
+      refine_st<false>(x, q + u * step, f[u]);
+    }
+  });
 }
 
-// phi += e; per-block partial ||e||^2 and ||phi||^2
-template <bool NT>
+// phi += e; per-block partial ||e||^2, ||phi||^2 and weighted sum of phi
+template <bool NT, int V>
 __device__ __forceinline__ void refine_update_body(double* __restrict__ phi,
                                                    const float* __restrict__ e32,
                                                    const RefineGeom& G, int block, int nblocks,
                                                    double* sh) {
   if (refine_skip(G.stats)) return;
-  double se = 0.0, sp = 0.0;
-  for (long long idx = block * (long long)REFINE_NT + threadIdx.x; idx < G.npts;
-       idx += (long long)nblocks * REFINE_NT) {
-    const double e = (double)refine_ld<NT>(&e32[idx]);
-    const double x = refine_ld<NT>(&phi[idx]) + e;
-    refine_st<NT>(x, &phi[idx]);
-    se += e * e;
-    sp += x * x;
-  }
-  block_sum2<REFINE_NT>(se, sp, sh);
+  double se = 0.0, sp = 0.0, sx = 0.0;
+  PlaneWalk at((block * (long long)REFINE_NT + threadIdx.x) * V, (long long)nblocks * REFINE_NT * V,
+               (long long)G.ax[0].n * G.ax[1].n);
+  refine_runs<V, 2>(G.npts, block, nblocks, [&](long long q, long long step, auto U) {
+    float e[U][V];
+    double x[U][V];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      refine_ld<NT>(e32, q + u * step, e[u]);
+      refine_ld<NT>(phi, q + u * step, x[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      double t = 0.0;
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        const double d = (double)e[u][i];
+        x[u][i] += d;
+        se += d * d;
+        sp += x[u][i] * x[u][i];
+        t += x[u][i];
+      }
+      refine_st<NT>(phi, q + u * step, x[u]);
+      sx += G.ax[2].h[at.k] * t;
+      at.advance();
+    }
+  });
+  se = block_sum<REFINE_NT>(se, sh);
+  sp = block_sum<REFINE_NT>(sp, sh);
+  sx = block_sum<REFINE_NT>(sx, sh);
   if (threadIdx.x == 0) {
-    G.stats[REFINE_PARTIALS + 2 * block] = se;
-    G.stats[REFINE_PARTIALS + 2 * block + 1] = sp;
+    G.stats[REFINE_PARTIALS + 3 * block] = se;
+    G.stats[REFINE_PARTIALS + 3 * block + 1] = sp;
+    G.stats[REFINE_PARTIALS + 3 * block + 2] = sx;
   }
 }
 
@@ -194,16 +289,15 @@ __device__ __forceinline__ void refine_update_body(double* __restrict__ phi,
 // remaining sweeps are skipped.  The margin covers a contraction that
 // differs between sweeps: the residual's spectrum is not f's, so the FP32
 // solve of a correction can be several times less accurate than the first.
-__device__ __forceinline__ void refine_status_body(double* stats, int nblocks, int sweep,
+__device__ __forceinline__ void refine_status_body(const RefineGeom& G, int nblocks, int sweep,
                                                    double tol, double* sh) {
+  double* stats = G.stats;
   if (refine_skip(stats)) return;
-  double a = 0.0, b = 0.0;
-  for (int i = threadIdx.x; i < nblocks; i += REFINE_NT) {
-    a += stats[REFINE_PARTIALS + 2 * i];
-    b += stats[REFINE_PARTIALS + 2 * i + 1];
-  }
-  block_sum2<REFINE_NT>(a, b, sh);
+  const double a = refine_partials(stats, 0, nblocks, sh);
+  const double b = refine_partials(stats, 1, nblocks, sh);
+  const double x = refine_partials(stats, 2, nblocks, sh);
   if (threadIdx.x == 0) {
+    stats[1] = x / G.weight;
     stats[4 + 2 * sweep] = a;
     stats[5 + 2 * sweep] = b;
     const double rel = b > 0.0 ? sqrt(a / b) : 0.0;
@@ -218,32 +312,42 @@ __device__ __forceinline__ void refine_status_body(double* stats, int nblocks, i
   }
 }
 
-// Launch shape of refine_residual_kernel: blocks of REFINE_NT points of an
-// xy plane, each marching through `kz` consecutive planes; `blocks` is the
-// block count rounded up to a multiple of 8 (see refine_residual_kernel).
+// Launch shape of refine_residual_kernel: blocks of REFINE_NT runs of v points,
+// 2^logtx runs along x by REFINE_NT / 2^logtx rows, each marching through `kz`
+// consecutive planes; `blocks` is the block count rounded up to a multiple of
+// 8 (see refine_residual_kernel).
 struct ResidualGrid {
-  int plane_blocks, kz, z_chunks, blocks;
+  int logtx, tiles_x, plane_blocks, kz, z_chunks, blocks;
 };
 
-inline ResidualGrid residual_grid(int nx, int ny, int nz) {
+inline ResidualGrid residual_grid(int nx, int ny, int nz, int v) {
   ResidualGrid r;
-  r.plane_blocks = (int)(((long long)nx * ny + REFINE_NT - 1) / REFINE_NT);
-  // about 2048 blocks in all, at least 4 planes each
-  r.kz = (int)std::max<long long>(4, ((long long)nz * r.plane_blocks + 2047) / 2048);
+  r.logtx = 0;
+  while (r.logtx < 6 && (v << r.logtx) < nx) ++r.logtx;
+  const int rows = REFINE_NT >> r.logtx;
+  r.tiles_x = (nx / v + (1 << r.logtx) - 1) >> r.logtx;
+  r.plane_blocks = r.tiles_x * ((ny + rows - 1) / rows);
+  // about two blocks per CU in all, at least 4 planes each: with the next plane
+  // read ahead, long marches gain more than more waves (channel 512 x 256 x
+  // 192: 512 blocks 112 us, 1024 125 us)
+  r.kz = (int)std::max<long long>(4, ((long long)nz * r.plane_blocks + 511) / 512);
   r.kz = std::min(r.kz, nz);
   r.z_chunks = (nz + r.kz - 1) / r.kz;
   r.blocks = (r.plane_blocks * r.z_chunks + 7) / 8 * 8;
   return r;
 }
 
-// e32 = (float)(f64 - A phi), FP64 arithmetic.  One thread per point of an
-// xy plane, marching through kz planes with phi of the planes below, at and
+// e32 = (float)(f64 - A phi), FP64 arithmetic.  One thread per V neighbouring x
+// points, marching through kz planes with phi of the planes below, at and
 // above in registers (each phi value is read from HBM about once; its x and
-// y neighbours come from the caches).  The 8 XCDs receive consecutive
+// y neighbours come from the caches: six loads for two points, where single
+// points take twelve), the next plane's values read while the current one is
+// computed.  A block covers several rows, so that most rows are fetched into
+// its CU once and not three times.  The 8 XCDs receive consecutive
 // blocks round-robin: block b works on chunk (b mod 8) * (blocks / 8) +
 // b / 8, so each XCD sweeps a contiguous run of rows, whose y neighbours its
 // own L2 holds.
-template <bool NT>
+template <bool NT, int V>
 __device__ __forceinline__ void refine_residual_body(const double* __restrict__ phi,
                                                      const double* __restrict__ f64,
                                                      float* __restrict__ e32, const RefineGeom& G,
@@ -252,86 +356,122 @@ __device__ __forceinline__ void refine_residual_body(const double* __restrict__ 
   const int chunk = (block % 8) * (rg.blocks / 8) + block / 8;
   if (chunk >= rg.plane_blocks * rg.z_chunks) return;
   const int nx = G.ax[0].n, ny = G.ax[1].n, nz = G.ax[2].n;
-  const int p = (chunk % rg.plane_blocks) * REFINE_NT + (int)threadIdx.x;
-  if (p >= nx * ny) return;
-  const int k0 = (chunk / rg.plane_blocks) * rg.kz;
+  const int zc = chunk / rg.plane_blocks, pb = chunk - zc * rg.plane_blocks;
+  const int ty = pb / rg.tiles_x, tx = pb - ty * rg.tiles_x;
+  const int i = ((tx << rg.logtx) + ((int)threadIdx.x & ((1 << rg.logtx) - 1))) * V;
+  const int j = ty * (REFINE_NT >> rg.logtx) + ((int)threadIdx.x >> rg.logtx);
+  if (i >= nx || j >= ny) return;
+  const int p = j * nx + i;
+  const int k0 = zc * rg.kz;
   const int k1 = min(k0 + rg.kz, nz);
-  const int i = p % nx, j = p / nx;
   const OpAxis& X = G.ax[0];
   const OpAxis& Y = G.ax[1];
   const OpAxis& Z = G.ax[2];
   // a_q phi_{q-1} + b_q phi_q + c_q phi_{q+1} per axis; a_0 / c_{n-1} are
   // the periodic wrap couplings (zero at a wall, where the ghost rule is in b)
-  const double ax = X.a[i], bx = X.b[i], cx = X.c[i];
+  double ax[V], bx[V], cx[V];
+#pragma unroll
+  for (int t = 0; t < V; ++t) {
+    ax[t] = X.a[i + t];
+    bx[t] = X.b[i + t];
+    cx[t] = X.c[i + t];
+  }
   const double ay = Y.a[j], by = Y.b[j], cy = Y.c[j];
-  const int xl = (i > 0 ? i - 1 : nx - 1) - i, xh = (i < nx - 1 ? i + 1 : 0) - i;
+  const int xl = (i > 0 ? i - 1 : nx - 1) - i, xh = (i + V < nx ? i + V : 0) - i;
   const int yl = ((j > 0 ? j - 1 : ny - 1) - j) * nx, yh = ((j < ny - 1 ? j + 1 : 0) - j) * nx;
   const long long plane = (long long)nx * ny;
-  double below = phi[(k0 > 0 ? k0 - 1 : nz - 1) * plane + p];
-  double at = phi[k0 * plane + p];
+  // run at point offset o (a multiple of V)
+  auto run = [&](long long o, double (&v)[V]) { refine_ld<false>(phi + o, 0, v); };
+  double below[V], at[V];
+  run((k0 > 0 ? k0 - 1 : nz - 1) * plane + p, below);
+  run(k0 * plane + p, at);
+  struct Plane {
+    double above[V], south[V], north[V], f[V], west, east;
+  };
+  auto read = [&](int k, Plane& q) {
+    const long long o = k * plane + p;
+    run(k < nz - 1 ? o + plane : (long long)p, q.above);
+    q.west = phi[o + xl];
+    q.east = phi[o + xh];
+    run(o + yl, q.south);
+    run(o + yh, q.north);
+    refine_ld<NT>(f64 + o, 0, q.f);
+  };
+  Plane cur, nxt;
+  read(k0, cur);
   for (int k = k0; k < k1; ++k) {
     const long long o = k * plane + p;
-    const double above = phi[(k < nz - 1 ? o + plane : (long long)p)];
-    const double opx = ax * phi[o + xl] + bx * at + cx * phi[o + xh];
-    const double opy = ay * phi[o + yl] + by * at + cy * phi[o + yh];
-    const double opz = Z.a[k] * below + Z.b[k] * at + Z.c[k] * above;
-    refine_st<NT>((float)(refine_ld<NT>(&f64[o]) - ((opx + opy) + opz)), &e32[o]);
-    below = at;
-    at = above;
+    read(min(k + 1, k1 - 1), nxt);
+    const double za = Z.a[k], zb = Z.b[k], zcc = Z.c[k];
+    float e[V];
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+      const double opx = ax[t] * (t > 0 ? at[t - 1] : cur.west) + bx[t] * at[t] +
+                         cx[t] * (t < V - 1 ? at[t + 1] : cur.east);
+      const double opy = ay * cur.south[t] + by * at[t] + cy * cur.north[t];
+      const double opz = za * below[t] + zb * at[t] + zcc * cur.above[t];
+      e[t] = (float)(cur.f[t] - ((opx + opy) + opz));
+    }
+    refine_st<NT>(e32 + o, 0, e);
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+      below[t] = at[t];
+      at[t] = cur.above[t];
+    }
+    cur = nxt;
   }
 }
 
-// ---- kernels for one plan
+// ---- kernels for one plan (V points per access: 2 where nx is even, else 1)
 
-__global__ void refine_init_kernel(double* stats) { refine_init_body(stats); }
-
+// the weighted sums of f; block 0 resets the status block
+template <int V>
 __global__ __launch_bounds__(REFINE_NT) void refine_wsum_kernel(const double* __restrict__ x,
-                                                                 RefineGeom G) {
-  __shared__ double sh[2 * REFINE_NT];
-  refine_wsum_body(x, G, blockIdx.x, gridDim.x, sh);
+                                                                 RefineGeom G, int init) {
+  __shared__ double sh[REFINE_NT];
+  if (init && blockIdx.x == 0) refine_init_body(G.stats);
+  refine_wsum_body<V>(x, G, blockIdx.x, gridDim.x, sh);
 }
 
-__global__ __launch_bounds__(REFINE_NT) void refine_mean_kernel(double* stats, int nblocks) {
-  __shared__ double sh[2 * REFINE_NT];
-  refine_mean_body(stats, nblocks, sh);
-}
-
-template <bool NT>
+// ... and so does the copy of f of a regular plan
+template <bool NT, int V>
 __global__ __launch_bounds__(REFINE_NT) void refine_prep_kernel(const double* __restrict__ rhs,
                                                                  double* __restrict__ f64,
                                                                  float* __restrict__ e32,
-                                                                 const double* stats, int project,
-                                                                 long long npts) {
-  refine_prep_body<NT>(rhs, f64, e32, stats, project, npts, blockIdx.x, gridDim.x);
+                                                                 RefineGeom G, int project) {
+  __shared__ double sh[REFINE_NT];
+  if (!project && blockIdx.x == 0) refine_init_body(G.stats);
+  refine_prep_body<NT, V>(rhs, f64, e32, G, project, blockIdx.x, gridDim.x, sh);
 }
 
+template <int V>
 __global__ __launch_bounds__(REFINE_NT) void refine_shift_kernel(double* __restrict__ x,
-                                                                  const double* stats,
-                                                                  long long npts) {
-  refine_shift_body(x, stats, npts, blockIdx.x, gridDim.x);
+                                                                  RefineGeom G, int summed) {
+  __shared__ double sh[REFINE_NT];
+  refine_shift_body<V>(x, G, summed, blockIdx.x, gridDim.x, sh);
 }
 
 // e32 = (float)(f64 - A phi), FP64 arithmetic (see refine_residual_body)
-template <bool NT>
+template <bool NT, int V>
 __global__ __launch_bounds__(REFINE_NT) void refine_residual_kernel(const double* __restrict__ phi,
                                                                      const double* __restrict__ f64,
                                                                      float* __restrict__ e32,
                                                                      RefineGeom G, ResidualGrid rg) {
-  refine_residual_body<NT>(phi, f64, e32, G, rg, blockIdx.x);
+  refine_residual_body<NT, V>(phi, f64, e32, G, rg, blockIdx.x);
 }
 
-template <bool NT>
+template <bool NT, int V>
 __global__ __launch_bounds__(REFINE_NT) void refine_update_kernel(double* __restrict__ phi,
                                                                    const float* __restrict__ e32,
                                                                    RefineGeom G) {
-  __shared__ double sh[2 * REFINE_NT];
-  refine_update_body<NT>(phi, e32, G, blockIdx.x, gridDim.x, sh);
+  __shared__ double sh[REFINE_NT];
+  refine_update_body<NT, V>(phi, e32, G, blockIdx.x, gridDim.x, sh);
 }
 
-__global__ __launch_bounds__(REFINE_NT) void refine_status_kernel(double* stats, int nblocks,
+__global__ __launch_bounds__(REFINE_NT) void refine_status_kernel(RefineGeom G, int nblocks,
                                                                    int sweep, double tol) {
-  __shared__ double sh[2 * REFINE_NT];
-  refine_status_body(stats, nblocks, sweep, tol, sh);
+  __shared__ double sh[REFINE_NT];
+  refine_status_body(G, nblocks, sweep, tol, sh);
 }
 
 // ---- kernels for a batch: job j owns blocks [first, first + count) of a
@@ -345,6 +485,7 @@ struct RefineJob {
   double* f64;
   float* e32;
   int singular;
+  int vec;              // points per access (2 or 1)
   int nb;               // blocks of the element-wise kernels
   ResidualGrid rg;
   int first_e;          // first block in the element-wise launches
@@ -365,31 +506,33 @@ __device__ __forceinline__ int refine_job_of(const RefineJob* __restrict__ jobs,
   return lo;
 }
 
-__global__ void refine_batch_init(const RefineJob* __restrict__ jobs) {
-  refine_init_body(jobs[blockIdx.x].G.stats);
+// f(points per access) of an instance, as a constant
+template <typename F>
+__device__ __forceinline__ void refine_width(const RefineJob& J, F&& f) {
+  if (J.vec == 2) f(std::integral_constant<int, 2>{});
+  else f(std::integral_constant<int, 1>{});
 }
 
 // the projection of f and the gauge of Phi touch singular instances only
 __global__ __launch_bounds__(REFINE_NT) void refine_batch_wsum(const RefineJob* __restrict__ jobs,
-                                                                int njobs) {
-  __shared__ double sh[2 * REFINE_NT];
+                                                                int njobs, int init) {
+  __shared__ double sh[REFINE_NT];
   const RefineJob& J = jobs[refine_job_of<false>(jobs, njobs, blockIdx.x)];
   if (!J.singular) return;
-  refine_wsum_body(J.phi, J.G, blockIdx.x - J.first_e, J.nb, sh);
-}
-
-__global__ __launch_bounds__(REFINE_NT) void refine_batch_mean(const RefineJob* __restrict__ jobs) {
-  __shared__ double sh[2 * REFINE_NT];
-  const RefineJob& J = jobs[blockIdx.x];
-  if (!J.singular) return;
-  refine_mean_body(J.G.stats, J.nb, sh);
+  const int block = blockIdx.x - J.first_e;
+  if (init && block == 0) refine_init_body(J.G.stats);
+  refine_width(J, [&](auto V) { refine_wsum_body<V>(J.phi, J.G, block, J.nb, sh); });
 }
 
 __global__ __launch_bounds__(REFINE_NT) void refine_batch_prep(const RefineJob* __restrict__ jobs,
                                                                 int njobs) {
+  __shared__ double sh[REFINE_NT];
   const RefineJob& J = jobs[refine_job_of<false>(jobs, njobs, blockIdx.x)];
-  refine_prep_body<false>(J.phi, J.f64, J.e32, J.G.stats, J.singular, J.G.npts, blockIdx.x - J.first_e,
-                   J.nb);
+  const int block = blockIdx.x - J.first_e;
+  if (!J.singular && block == 0) refine_init_body(J.G.stats);
+  refine_width(J, [&](auto V) {
+    refine_prep_body<false, V>(J.phi, J.f64, J.e32, J.G, J.singular, block, J.nb, sh);
+  });
 }
 
 // sweep `sweep`: the residual, or the stop of an instance at its limit
@@ -401,28 +544,34 @@ __global__ __launch_bounds__(REFINE_NT) void refine_batch_residual(const RefineJ
     if (block == 0 && threadIdx.x == 0) J.G.stats[0] = 1.0;
     return;
   }
-  refine_residual_body<false>(J.phi, J.f64, J.e32, J.G, J.rg, block);
+  refine_width(J, [&](auto V) { refine_residual_body<false, V>(J.phi, J.f64, J.e32, J.G, J.rg, block); });
 }
 
 __global__ __launch_bounds__(REFINE_NT) void refine_batch_update(const RefineJob* __restrict__ jobs,
                                                                   int njobs) {
-  __shared__ double sh[2 * REFINE_NT];
+  __shared__ double sh[REFINE_NT];
   const RefineJob& J = jobs[refine_job_of<false>(jobs, njobs, blockIdx.x)];
-  refine_update_body<false>(J.phi, J.e32, J.G, blockIdx.x - J.first_e, J.nb, sh);
+  refine_width(J, [&](auto V) {
+    refine_update_body<false, V>(J.phi, J.e32, J.G, blockIdx.x - J.first_e, J.nb, sh);
+  });
 }
 
 __global__ __launch_bounds__(REFINE_NT) void refine_batch_status(const RefineJob* __restrict__ jobs,
                                                                   int sweep) {
-  __shared__ double sh[2 * REFINE_NT];
+  __shared__ double sh[REFINE_NT];
   const RefineJob& J = jobs[blockIdx.x];
-  refine_status_body(J.G.stats, J.nb, sweep, J.tol, sh);
+  refine_status_body(J.G, J.nb, sweep, J.tol, sh);
 }
 
+// (an instance limited to one FP32 solve has no update to take its mean from)
 __global__ __launch_bounds__(REFINE_NT) void refine_batch_shift(const RefineJob* __restrict__ jobs,
                                                                  int njobs) {
+  __shared__ double sh[REFINE_NT];
   const RefineJob& J = jobs[refine_job_of<false>(jobs, njobs, blockIdx.x)];
   if (!J.singular) return;
-  refine_shift_body(J.phi, J.G.stats, J.G.npts, blockIdx.x - J.first_e, J.nb);
+  refine_width(J, [&](auto V) {
+    refine_shift_body<V>(J.phi, J.G, J.max_iters == 1, blockIdx.x - J.first_e, J.nb, sh);
+  });
 }
 
 }  // namespace poisson_dev
