@@ -284,19 +284,23 @@ __global__ __launch_bounds__(RK3_NT) void rk3_predict_tiled_kernel(RK3Args A) {
 // needs u* on its high x face and v* on its high y face, which for the
 // tile's last column and row belong to the neighbouring tiles, so the
 // tile holds a two-cell halo on its high sides (rows and columns of
-// 64 + 3 and 4 + 3 slots) and recomputes those faces: wave 0 the cells of
-// the row beyond the tile, four lanes of wave 1 the column beyond it,
+// 64 + 3 and 8 + 3 slots) and recomputes those faces: wave 0 the cells of
+// the row beyond the tile, eight lanes of wave 1 the column beyond it,
 // with the same cell function as the tile's own faces.  u* and v* of a
 // plane pass to the neighbouring threads through a double-buffered LDS
 // exchange; w* of the plane above is the next iteration's own value, so
 // plane k's divergence is formed in iteration k + 1, and each block
 // computes one plane beyond its z range (w* only is used there).  The
 // right-hand side costs 8 B per cell instead of the 32 B of a separate
-// sweep over u*.
-static constexpr int RK3D_HX = RK3_TX + 3, RK3D_HY = RK3_TY + 3;  // lx in [-1, TX+1], ly in [-1, TY+1]
+// sweep over u*.  Eight rows per tile, one block per CU (112 KB
+// of LDS): with four rows and two blocks 11 / 8 of the rows read
+// become 7 / 4, and an RK3 step takes 17.95 instead of 17.44 ms at 512^3
+// and 2.25 instead of 2.20 ms at 256^3.
+static constexpr int RK3D_TY = 8, RK3D_NT = RK3_TX * RK3D_TY;
+static constexpr int RK3D_HX = RK3_TX + 3, RK3D_HY = RK3D_TY + 3;  // lx in [-1, TX+1], ly in [-1, TY+1]
 static constexpr int RK3D_PL = RK3D_HX * RK3D_HY;
-static constexpr int RK3D_HALO = RK3D_PL - RK3_TX * RK3_TY;
-static_assert(RK3D_HALO <= RK3_NT && RK3_TX + RK3_TY <= RK3_NT, "fused tile shape");
+static constexpr int RK3D_HALO = RK3D_PL - RK3_TX * RK3D_TY;
+static_assert(RK3D_HALO <= RK3D_NT && RK3_TX + RK3D_TY <= RK3D_NT, "fused tile shape");
 
 // CORRECT: the previous substep's projection is applied as the planes
 // arrive instead of in a sweep of its own: the kernel reads u* and Phi of
@@ -307,28 +311,49 @@ static_assert(RK3D_HALO <= RK3_NT && RK3_TX + RK3_TY <= RK3_NT, "fused tile shap
 // read p).  The z gradient takes Phi of the plane below from the previous
 // fetch of the same slot.
 //
-// FULL (nx a multiple of RK3_TX, ny of RK3_TY, nz of RK3_KC): every cell of
-// every tile exists, so no lane skips a load or a store in the z loop, and
-// the compiler's waits for a plane's reads leave the later reads and the
-// stores in flight.  The previous AD of a plane (the own cell's, and for
-// the edge lanes the edge cell's) is read before the plane three ahead,
+// FULL: no lane skips a load or a store in the z loop, so the compiler's waits
+// for a plane's reads leave the later reads and the stores in flight.  Lanes
+// past a smaller tile's cells repeat its last cell's work in every respect and
+// store the same values to the same addresses (working on their wrapped cells
+// instead would store other roundings: a tile's last row takes v* above it
+// from the second copy of the cell function).  The previous AD
+// of a plane (the own cell's, and for the edge lanes the edge cell's) is read
+// before the plane three ahead,
 // the halo reads of lanes without a halo slot read their own cell instead,
 // and the first plane and the last two are peeled off the loop (no
-// divergence yet; no plane left to read; w* only).  The other shapes keep
-// the general loop, in which these reads and stores sit behind branches.
+// divergence yet; no plane left to read; w* only), so a z range has two planes
+// at least.  Every shape takes this loop; POISSON_RK3_GENERAL=1 runs the
+// general one, with its reads and stores behind branches, for tests.  The
+// three predictions of a step, general loop on 4-row tiles and 64-plane
+// ranges -> this one: 340 + 403 + 349 -> 278 + 346 + 296 us at
+// 192 x 192 x 400, 913 + 1024 + 842 -> 746 + 936 + 723 us at 324^3,
+// 85 + 97 + 94 -> 19 + 24 + 22 us at 100 x 96 x 90.
 template <bool READ_PREV, bool WRITE_AD, bool CORRECT, bool FULL>
-__global__ __launch_bounds__(RK3_NT) void rk3_predict_div_kernel(RK3Args A, double* __restrict__ rhs,
+__global__ __launch_bounds__(RK3D_NT) void rk3_predict_div_kernel(RK3Args A, double* __restrict__ rhs,
                                                                  double inv_gdt) {
   __shared__ double ring[4][4][RK3D_PL];             // [plane slot][u, v, w, p][slot]
-  __shared__ double xu[2][RK3_TY][RK3_TX + 1];        // u* of a plane: the tile and column TX
-  __shared__ double xv[2][RK3_TY + 1][RK3_TX];        // v* of a plane: the tile and row TY
+  __shared__ double xu[2][RK3D_TY][RK3_TX + 1];        // u* of a plane: the tile and column TX
+  __shared__ double xv[2][RK3D_TY + 1][RK3_TX];        // v* of a plane: the tile and row TY
   const int nx = A.nx, ny = A.ny, nz = A.nz;
   const long long N = A.npts;
   const long long plane = (long long)nx * ny;
   const int t = threadIdx.x;
-  const int tx = t & (RK3_TX - 1), ty = t / RK3_TX;
-  const int i0 = blockIdx.x * RK3_TX, j0 = blockIdx.y * RK3_TY, k0 = blockIdx.z * RK3_KC;
-  const int kend = min(k0 + RK3_KC, nz);
+  // Blocks go round the eight XCDs, each with an L2 of its own.  The xy tiles
+  // of a z range are dealt so that an XCD gets neighbouring ones and reads
+  // their common halo once (256^3: 2.29 -> 2.20 ms per step).  Where a row of
+  // tiles is a multiple of eight, a column of tiles is on one XCD as it is,
+  // and that order is kept (512^3: 17.85 -> 17.44 ms; 450 x 100 x 360 lost
+  // 2 % by it).
+  const int gx = gridDim.x, ntile = gx * (int)gridDim.y, b0 = blockIdx.x + gx * blockIdx.y;
+  const int tile = (gx & 7) == 0 ? b0 : (b0 & 7) * (ntile >> 3) + min(b0 & 7, ntile & 7) + (b0 >> 3);
+  const int bx = tile % gx, by = tile / gx, bz = blockIdx.z;
+  const int i0 = bx * RK3_TX, j0 = by * RK3D_TY, k0 = (int)(((long long)bz * nz) / gridDim.z);
+  const int kend = (int)(((long long)(bz + 1) * nz) / gridDim.z);
+  // the last tiles along x and y hold fewer cells (columns, rows); the lanes
+  // past them do the last cell's work once more
+  const int cols = min(RK3_TX, nx - i0), rows = min(RK3D_TY, ny - j0);
+  const int tx = min(t & (RK3_TX - 1), cols - 1), ty = min(t / RK3_TX, rows - 1);
+  const bool active = (t & (RK3_TX - 1)) < cols && t / RK3_TX < rows;
   auto wrap = [](int a, int n) { a %= n; return a < 0 ? a + n : a; };
   auto slot_of = [](int lx, int ly) { return (ly + 1) * RK3D_HX + lx + 1; };
   auto off_of = [&](int lx, int ly) {
@@ -336,35 +361,35 @@ __global__ __launch_bounds__(RK3_NT) void rk3_predict_div_kernel(RK3Args A, doub
   };
   const int own_slot = slot_of(tx, ty);
   const long long own_off = off_of(tx, ty);
-  // halo slots, row by row: row -1 (67), rows 0..TY-1 (columns -1, TX, TX+1), rows TY, TY+1 (67 each)
+  // halo slots, row by row: row -1, rows 0 to rows - 1 (columns -1, cols, cols + 1), rows `rows` and `rows` + 1
+  const int hw = cols + 3;
   int halo_slot = -1;
   long long halo_off = 0;
-  if (t < RK3D_HALO) {
+  if (t < 3 * hw + 3 * rows) {
     int lx, ly;
-    if (t < RK3D_HX) { ly = -1; lx = t - 1; }
-    else if (t < RK3D_HX + 3 * RK3_TY) {
-      const int r = t - RK3D_HX;
+    if (t < hw) { ly = -1; lx = t - 1; }
+    else if (t < hw + 3 * rows) {
+      const int r = t - hw;
       ly = r / 3;
-      lx = r % 3 == 0 ? -1 : RK3_TX - 1 + r % 3;
+      lx = r % 3 == 0 ? -1 : cols - 1 + r % 3;
     } else {
-      const int r = t - RK3D_HX - 3 * RK3_TY;
-      ly = RK3_TY + r / RK3D_HX;
-      lx = r % RK3D_HX - 1;
+      const int r = t - hw - 3 * rows, over = r >= hw;
+      ly = rows + over;
+      lx = r - over * hw - 1;
     }
     halo_slot = slot_of(lx, ly);
     halo_off = off_of(lx, ly);
   }
-  // edge faces: wave 0 the row TY (v* there), lanes 0..TY-1 of wave 1 the column TX (u* there)
+  // edge faces: wave 0 the row `rows` (v* there), the first lanes of wave 1 the column `cols` (u* there)
   int edge_slot = -1;
   long long edge_off = 0;
-  if (t < RK3_TX) {
-    edge_slot = slot_of(t, RK3_TY);
-    edge_off = off_of(t, RK3_TY);
-  } else if (t < RK3_TX + RK3_TY) {
-    edge_slot = slot_of(RK3_TX, t - RK3_TX);
-    edge_off = off_of(RK3_TX, t - RK3_TX);
+  if (t < cols) {
+    edge_slot = slot_of(t, rows);
+    edge_off = off_of(t, rows);
+  } else if (t >= RK3_TX && t < RK3_TX + rows) {
+    edge_slot = slot_of(cols, t - RK3_TX);
+    edge_off = off_of(cols, t - RK3_TX);
   }
-  const bool active = i0 + tx < nx && j0 + ty < ny;
   // fields read per slot: u, v, w, p; with CORRECT also Phi and its x and y
   // neighbours below the slot
   constexpr int NF = CORRECT ? 7 : 4;
@@ -521,8 +546,8 @@ __global__ __launch_bounds__(RK3_NT) void rk3_predict_div_kernel(RK3Args A, doub
         xv[b][ty][tx] = r.star[1];
         if (edge_slot >= 0) {
           const RK3Cell e = rk3_cell<RK3D_PL, RK3D_HX>(Rm, R0, Rp, edge_slot, A, eprev);
-          if (t < RK3_TX) xv[b][RK3_TY][t] = e.star[1];
-          else xu[b][t - RK3_TX][RK3_TX] = e.star[0];
+          if (t < RK3_TX) xv[b][rows][t] = e.star[1];
+          else xu[b][t - RK3_TX][cols] = e.star[0];
         }
       }
       star_below[0] = r.star[0];
@@ -584,8 +609,8 @@ __global__ __launch_bounds__(RK3_NT) void rk3_predict_div_kernel(RK3Args A, doub
         double eprev[3];
         load_prev(edge_off + base, eprev);
         const RK3Cell e = rk3_cell<RK3D_PL, RK3D_HX>(Rm, R0, Rp, edge_slot, A, eprev);
-        if (t < RK3_TX) xv[b][RK3_TY][t] = e.star[1];
-        else xu[b][t - RK3_TX][RK3_TX] = e.star[0];
+        if (t < RK3_TX) xv[b][rows][t] = e.star[1];
+        else xu[b][t - RK3_TX][cols] = e.star[0];
       }
     }
     star_below[0] = r.star[0];

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -159,7 +160,7 @@ struct poisson_plan {
   bool generic_tri = false;    // POISSON_GENERIC_TRI=1: size-generic elimination kernel only
   int grid_cap = 0;            // POISSON_GRID_CAP=B: at most B blocks per stage launch (0: none)
   int rk3_kernel = 0;          // POISSON_RK3_KERNEL: 0 fused (default), 1 "tiled", 2 "simple"
-  bool rk3_general = false;    // POISSON_RK3_GENERAL=1: the fused kernel's general z loop on whole tiles too
+  bool rk3_general = false;    // POISSON_RK3_GENERAL=1: the fused kernel's general z loop
   bool plane_off = false;      // POISSON_PLANE=0: no small-plane transforms
   char* plane_mats = nullptr;  // small grids: dense transform matrices (FP64, then FP32)
   size_t plane_off_f = 0;      // byte offset of the FP32 copy in plane_mats
@@ -1757,29 +1758,49 @@ static dim3 rk3_tiles(const RK3Args& A) {
   return dim3((A.nx + RK3_TX - 1) / RK3_TX, (A.ny + RK3_TY - 1) / RK3_TY, (A.nz + RK3_KC - 1) / RK3_KC);
 }
 
+// Tiles of the fused prediction.  One block is resident per CU; a z range costs
+// its planes and four more that fill the pipeline, and the grid runs in rounds
+// of 256 blocks: the number of ranges with the fewest planes in sequence is
+// taken.  A range has 128 planes at most (RK3 step at 324^3 with at most 64:
+// 5.44 ms, 128: 5.35, 256: 5.33; at 512^3 17.48, 17.44, 17.49) and two at
+// least, which the kernel's peeled steps need.
+static dim3 rk3_div_tiles(const RK3Args& A) {
+  const int tx = (A.nx + RK3_TX - 1) / RK3_TX, ty = (A.ny + RK3D_TY - 1) / RK3D_TY;
+  const int fewest = (A.nz + 127) / 128, most = std::min(std::max(fewest, A.nz / 2), fewest + 255);
+  int ranges = fewest;
+  long long least = LLONG_MAX;
+  for (int n = fewest; n <= most; ++n) {
+    const long long rounds = ((long long)tx * ty * n + 255) / 256;
+    const long long planes = rounds * ((A.nz + n - 1) / n + 4);
+    if (planes < least) {
+      least = planes;
+      ranges = n;
+    }
+  }
+  return dim3(tx, ty, ranges);
+}
+
 // The fused prediction of substep k (with the previous substep's
 // correction when `correct`); rhs = div(u*) / (gamma_k dt).
 static int launch_predict_div(const RK3Args& A, int k, bool correct, double* rhs, hipStream_t st,
                               bool general) {
-  const dim3 tiles = rk3_tiles(A);
+  const dim3 tiles = rk3_div_tiles(A);
   const double inv_gdt = 1.0 / A.g_dt;
-  // whole tiles and z ranges: the branch-free form of the z loop
-  const bool full = A.nx % RK3_TX == 0 && A.ny % RK3_TY == 0 && A.nz % RK3_KC == 0 && !general;
   auto go = [&](auto full_c) {
     constexpr bool F = decltype(full_c)::value;
     if (k == 1)
-      hipLaunchKernelGGL((rk3_predict_div_kernel<false, true, false, F>), tiles, dim3(RK3_NT), 0, st, A, rhs, inv_gdt);
+      hipLaunchKernelGGL((rk3_predict_div_kernel<false, true, false, F>), tiles, dim3(RK3D_NT), 0, st, A, rhs, inv_gdt);
     else if (k == 2 && !correct)
-      hipLaunchKernelGGL((rk3_predict_div_kernel<true, true, false, F>), tiles, dim3(RK3_NT), 0, st, A, rhs, inv_gdt);
+      hipLaunchKernelGGL((rk3_predict_div_kernel<true, true, false, F>), tiles, dim3(RK3D_NT), 0, st, A, rhs, inv_gdt);
     else if (k == 2)
-      hipLaunchKernelGGL((rk3_predict_div_kernel<true, true, true, F>), tiles, dim3(RK3_NT), 0, st, A, rhs, inv_gdt);
+      hipLaunchKernelGGL((rk3_predict_div_kernel<true, true, true, F>), tiles, dim3(RK3D_NT), 0, st, A, rhs, inv_gdt);
     else if (!correct)
-      hipLaunchKernelGGL((rk3_predict_div_kernel<true, false, false, F>), tiles, dim3(RK3_NT), 0, st, A, rhs, inv_gdt);
+      hipLaunchKernelGGL((rk3_predict_div_kernel<true, false, false, F>), tiles, dim3(RK3D_NT), 0, st, A, rhs, inv_gdt);
     else
-      hipLaunchKernelGGL((rk3_predict_div_kernel<true, false, true, F>), tiles, dim3(RK3_NT), 0, st, A, rhs, inv_gdt);
+      hipLaunchKernelGGL((rk3_predict_div_kernel<true, false, true, F>), tiles, dim3(RK3D_NT), 0, st, A, rhs, inv_gdt);
   };
-  if (full) go(std::true_type{});
-  else go(std::false_type{});
+  if (general) go(std::false_type{});
+  else go(std::true_type{});
   HIP_TRY(hipGetLastError());
   return POISSON_OK;
 }
