@@ -183,9 +183,14 @@ __device__ __forceinline__ lptr<T> as_lds(T* p) {
 // Barrier for hand-offs through LDS between the waves of a block.  Unlike
 // __syncthreads() it orders LDS accesses only: the wave waits for its own LDS
 // operations, not for its global loads and stores, so a tile's stores (and
-// reads of a next tile already issued) stay in flight across it.
+// reads of a next tile already issued) stay in flight across it.  The wait is
+// spelled out: the one that the release fence stands for was dropped by the
+// compiler where the barrier is the first thing in a loop whose body ends with
+// LDS writes (its pass over the loop's entry finds nothing pending and removes
+// it), and another wave then read a tile's last values before they arrived.
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
