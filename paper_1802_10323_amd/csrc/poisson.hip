@@ -1657,10 +1657,16 @@ static ProjGeom proj_geom(const poisson_plan* p) {
   return G;
 }
 
-// z-marching tiles of the projection kernels: 64 x 4 columns, PROJ_KC planes
+// z-marching tiles of the projection kernels: 64 x 4 columns, z ranges of at
+// most PROJ_KC planes; shorter ones, down to four planes, where the grid would
+// have fewer than 2048 blocks (a range reads one plane of Phi or w more than it
+// has: the update of 128^3 cells 40 -> 28 us, of 192 x 144 x 128 56 -> 45 us,
+// with at least eight planes the same within the noise).
 static dim3 proj_tiles(const poisson_plan* p) {
-  return dim3((p->dims[0] + PROJ_TX - 1) / PROJ_TX, (p->dims[1] + PROJ_TY - 1) / PROJ_TY,
-              (p->dims[2] + PROJ_KC - 1) / PROJ_KC);
+  const int tx = (p->dims[0] + PROJ_TX - 1) / PROJ_TX, ty = (p->dims[1] + PROJ_TY - 1) / PROJ_TY, nz = p->dims[2];
+  const long long tiles = (long long)tx * ty;
+  const int longest = (nz + PROJ_KC - 1) / PROJ_KC, most = std::max(1, nz / 4);
+  return dim3(tx, ty, std::max(longest, (int)std::min<long long>((2047 + tiles) / tiles, most)));
 }
 
 // u = u_in - gamma_dt grad(phi), p += phi (z-marching tiles; in place when u_in == u)

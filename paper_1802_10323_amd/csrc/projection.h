@@ -63,8 +63,8 @@ __global__ __launch_bounds__(PROJ_NT) void proj_rhs_kernel(const double* __restr
   const long long plane = (long long)nx * ny;
   const int i = blockIdx.x * PROJ_TX + (threadIdx.x & (PROJ_TX - 1));
   const int j = blockIdx.y * PROJ_TY + threadIdx.x / PROJ_TX;
-  const int k0 = blockIdx.z * PROJ_KC;
-  const int kend = min(k0 + PROJ_KC, nz);
+  const int k0 = (int)((long long)blockIdx.z * nz / gridDim.z);
+  const int kend = (int)((long long)(blockIdx.z + 1) * nz / gridDim.z);
   if (i >= nx || j >= ny) return;
   const int ip = G.ax[0].walled || i + 1 < nx ? i + 1 : 0;     // high x face
   const int jp = G.ax[1].walled || j + 1 < ny ? j + 1 : 0;     // high y face
@@ -101,14 +101,20 @@ __global__ __launch_bounds__(PROJ_NT) void proj_rhs_kernel(const double* __restr
 // u = u_in - gdt grad(phi) on every face, p += phi at every cell; in place
 // when u_in == u (each face is read before it is written, by the same
 // thread, and by no other).  z-marching: a block owns a 64 x 4 tile of
-// (i, j) columns and PROJ_KC consecutive planes; each thread walks its
+// (i, j) columns and at most PROJ_KC consecutive planes; each thread walks its
 // column upward with Phi of the cell below in a register, so the z
 // gradient reads no other plane (the x and y neighbours come from the
 // lines the adjacent lanes and rows load).  The face values and p, each
 // read and written by one thread only, take the nontemporal hint; Phi,
-// which the neighbouring lanes read again, does not.  Measured: the
-// update on the 512 x 256 x 192 channel 0.378-0.383 -> 0.361-0.362 ms, an
-// RK3 step of the periodic 512^3 Taylor-Green vortex 17.96 -> 17.87 ms.
+// which the neighbouring lanes read again, does not.  No lane skips a
+// load or a store on account of its place in the grid: at a wall the
+// neighbour's address is the cell's own and the gradient is selected, and
+// the high wall faces are behind uniform branches, so a plane's waits leave
+// the next plane's reads and the stores in flight.  Bound by HBM.  Measured,
+// branches per lane -> selects: 114 -> 92 us on 512 x 128 x 128 (P, NN, NN;
+// 6.5 TB/s), 329 -> 307 us on 512 x 256 x 192 (P, P, NN; 5.9 TB/s), 128 ->
+// 101 us on 270 x 150 x 162 (NN, P, ND), 1.63 -> 1.60 ms on the periodic
+// 512^3 (6.0 TB/s).
 __global__ __launch_bounds__(PROJ_NT) void proj_update_zmarch_kernel(
     const double* __restrict__ phi, double gdt, const double* u_in, const double* v_in,
     const double* w_in, double* u, double* v, double* w, double* __restrict__ p, ProjGeom G) {
@@ -118,15 +124,24 @@ __global__ __launch_bounds__(PROJ_NT) void proj_update_zmarch_kernel(
   const long long plane = (long long)nx * ny;
   const int i = blockIdx.x * PROJ_TX + (threadIdx.x & (PROJ_TX - 1));
   const int j = blockIdx.y * PROJ_TY + threadIdx.x / PROJ_TX;
-  const int k0 = blockIdx.z * PROJ_KC;
-  const int kend = min(k0 + PROJ_KC, nz);
+  const int k0 = (int)((long long)blockIdx.z * nz / gridDim.z);
+  const int kend = (int)((long long)(blockIdx.z + 1) * nz / gridDim.z);
   if (i >= nx || j >= ny) return;
   const ProjAxis& X = G.ax[0];
   const ProjAxis& Y = G.ax[1];
   const ProjAxis& Z = G.ax[2];
   const long long col = i + (long long)nx * j;
-  const bool xh = X.walled && i == nx - 1;   // this column also owns the high wall faces
-  const bool yh = Y.walled && j == ny - 1;
+  // columns on a wall: the low wall face's gradient is 2 Phi / h (Dirichlet)
+  // or none (Neumann), and the last column also owns the high wall face,
+  // which a Neumann wall leaves as it is (nothing to do in place)
+  const bool xl = X.walled && i == 0, yl = Y.walled && j == 0;
+  const bool xkeep = xl && !X.lo_dirichlet, ykeep = yl && !Y.lo_dirichlet;
+  const bool xwall = X.walled && (X.hi_dirichlet || u_in != u), xh = xwall && i == nx - 1;
+  const bool ywall = Y.walled && (Y.hi_dirichlet || v_in != v), yh = ywall && j == ny - 1;
+  const bool zwall = Z.walled && (Z.hi_dirichlet || w_in != w);
+  const int dx = i > 0 ? -1 : X.walled ? 0 : nx - 1;           // the low x and y neighbours of Phi
+  const long long dy = j > 0 ? -nx : Y.walled ? 0 : plane - nx;
+  const double idx = X.inv_dc[i], idy = Y.inv_dc[j];
   // the inputs of one plane; the next plane's are read before this one's
   // results are stored, so a thread keeps two planes' reads in flight
   struct In {
@@ -138,16 +153,17 @@ __global__ __launch_bounds__(PROJ_NT) void proj_update_zmarch_kernel(
     In r;
     const long long c = col + plane * k;
     r.ph = phi[c];
-    r.phx = i > 0 ? phi[c - 1] : (!X.walled ? phi[c + nx - 1] : 0.0);
-    r.phy = j > 0 ? phi[c - nx] : (!Y.walled ? phi[c + (long long)nx * (ny - 1)] : 0.0);
+    r.phx = phi[c + dx];
+    r.phy = phi[c + dy];
     const long long fu = face_u(k), fv = face_v(k);
     r.u0 = __builtin_nontemporal_load(&u_in[fu]);
     r.v0 = __builtin_nontemporal_load(&v_in[fv]);
     r.w0 = __builtin_nontemporal_load(&w_in[c]);
     r.p0 = __builtin_nontemporal_load(&p[c]);
-    r.uh = xh ? u_in[fu + 1] : 0.0;
-    r.vh = yh ? v_in[fv + nx] : 0.0;
-    r.wh = Z.walled && k == nz - 1 ? w_in[c + plane] : 0.0;
+    r.uh = r.vh = r.wh = 0.0;
+    if (xwall) r.uh = u_in[fu + (xh ? 1 : 0)];
+    if (ywall) r.vh = v_in[fv + (yh ? nx : 0)];
+    if (zwall && k == nz - 1) r.wh = w_in[c + plane];
     return r;
   };
   // Phi below the first plane: the plane under it, the periodic wrap, or none (a wall)
@@ -161,25 +177,18 @@ __global__ __launch_bounds__(PROJ_NT) void proj_update_zmarch_kernel(
     const long long c = col + plane * k;
     const double ph = cur.ph;
     // low-face gradients; a Neumann wall face keeps its velocity
-    bool ax_ = true, ay_ = true, az_ = true;
-    double gx, gy, gz;
-    if (i > 0 || !X.walled) gx = (ph - cur.phx) * X.inv_dc[i];
-    else if (!X.lo_dirichlet) { ax_ = false; gx = 0.0; }
-    else gx = 2.0 * ph * X.inv_dc[0];
-    if (j > 0 || !Y.walled) gy = (ph - cur.phy) * Y.inv_dc[j];
-    else if (!Y.lo_dirichlet) { ay_ = false; gy = 0.0; }
-    else gy = 2.0 * ph * Y.inv_dc[0];
-    if (k > 0 || !Z.walled) gz = (ph - below) * Z.inv_dc[k];
-    else if (!Z.lo_dirichlet) { az_ = false; gz = 0.0; }
-    else gz = 2.0 * ph * Z.inv_dc[0];
+    const bool zl = Z.walled && k == 0;
+    const double gx = (xl ? 2.0 * ph : ph - cur.phx) * idx;
+    const double gy = (yl ? 2.0 * ph : ph - cur.phy) * idy;
+    const double gz = (zl ? 2.0 * ph : ph - below) * Z.inv_dc[k];
     const long long fu = face_u(k), fv = face_v(k);
-    __builtin_nontemporal_store(ax_ ? cur.u0 - gdt * gx : cur.u0, &u[fu]);
-    __builtin_nontemporal_store(ay_ ? cur.v0 - gdt * gy : cur.v0, &v[fv]);
-    __builtin_nontemporal_store(az_ ? cur.w0 - gdt * gz : cur.w0, &w[c]);
+    __builtin_nontemporal_store(xkeep ? cur.u0 : cur.u0 - gdt * gx, &u[fu]);
+    __builtin_nontemporal_store(ykeep ? cur.v0 : cur.v0 - gdt * gy, &v[fv]);
+    __builtin_nontemporal_store(zl && !Z.lo_dirichlet ? cur.w0 : cur.w0 - gdt * gz, &w[c]);
     // high wall faces: Dirichlet gradient -2 phi_edge / h_edge; Neumann unchanged
-    if (xh) u[fu + 1] = X.hi_dirichlet ? cur.uh - gdt * (-2.0 * ph * X.inv_dc[nx]) : cur.uh;
-    if (yh) v[fv + nx] = Y.hi_dirichlet ? cur.vh - gdt * (-2.0 * ph * Y.inv_dc[ny]) : cur.vh;
-    if (Z.walled && k == nz - 1)
+    if (xwall && xh) u[fu + 1] = X.hi_dirichlet ? cur.uh - gdt * (-2.0 * ph * X.inv_dc[nx]) : cur.uh;
+    if (ywall && yh) v[fv + nx] = Y.hi_dirichlet ? cur.vh - gdt * (-2.0 * ph * Y.inv_dc[ny]) : cur.vh;
+    if (zwall && k == nz - 1)
       w[c + plane] = Z.hi_dirichlet ? cur.wh - gdt * (-2.0 * ph * Z.inv_dc[nz]) : cur.wh;
     __builtin_nontemporal_store(cur.p0 + ph, &p[c]);
     below = ph;
