@@ -258,9 +258,10 @@ int batch_autotune(poisson_batch* batch, int reps, hipStream_t stream, double* r
  * length 512, strided eliminations) while their entry is neither set by hand
  * nor tuned.  The autotuner times them too, and solves keep them where they
  * beat every variant; the entry then still names the fastest variant.
- * pressure_correction always runs the variants and the size-generic kernels,
- * so that its results keep their bits.  Plans and batches read the
- * table when they launch (batches when they are bound; batches use the
+ * pressure_correction always runs the variants and the size-generic kernels
+ * for its transforms and eliminations: its Phi on an already divergence-free
+ * velocity is the solve of rounding noise, which any other rounding changes.
+ * Plans and batches read the table when they launch (batches when they are bound; batches use the
  * synchronous variants only: transforms 0-3, elimination 0-1). */
 
 /* Time every variant of this plan's kernels (both transformed axes and the
