@@ -114,7 +114,7 @@ __global__ __launch_bounds__(PROJ_NT) void proj_rhs_kernel(const double* __restr
 // branches per lane -> selects: 114 -> 92 us on 512 x 128 x 128 (P, NN, NN;
 // 6.5 TB/s), 329 -> 307 us on 512 x 256 x 192 (P, P, NN; 5.9 TB/s), 128 ->
 // 101 us on 270 x 150 x 162 (NN, P, ND), 1.63 -> 1.60 ms on the periodic
-// 512^3 (6.0 TB/s).
+// 512^3 (6.0 TB/s; out of place, at the end of a time step, 1.82 -> 1.85).
 __global__ __launch_bounds__(PROJ_NT) void proj_update_zmarch_kernel(
     const double* __restrict__ phi, double gdt, const double* u_in, const double* v_in,
     const double* w_in, double* u, double* v, double* w, double* __restrict__ p, ProjGeom G) {
