@@ -1970,6 +1970,7 @@ struct poisson_batch {
   RefineJob* drefine = nullptr;       // refined batch: per-instance refinement jobs (device)
   int refine_eblocks = 0;             // blocks of its element-wise launches
   int refine_rblocks = 0;             // blocks of its residual launch
+  std::vector<int> iters;             // iteration limits that the refinement jobs hold
   bool bound = false;
   hipStream_t cap = nullptr;          // private stream for graph capture
   hipGraph_t graph = nullptr;
@@ -2112,8 +2113,9 @@ extern "C" poisson_batch* batch_create(poisson_plan* const* plans, int count) {
 }
 
 // Job tables for the bound fields to the device (synchronous).  The
-// captured launches carry the LDS size, grid and item count of each step:
-// when the variants changed them, capture again at the next launch.
+// captured launches carry the LDS size, grid and item count of each step and
+// follow the iteration limits: when these changed, capture again at the next
+// launch.
 static int batch_upload(poisson_batch* b) {
   size_t lds_before[kMaxSteps];
   int items_before[kMaxSteps];
@@ -2121,13 +2123,17 @@ static int batch_upload(poisson_batch* b) {
   std::memcpy(items_before, b->items, sizeof(items_before));
   std::vector<char> host;
   batch_jobs(b, b->rhs.data(), host);
-  if (b->exec && (std::memcmp(lds_before, b->lds, sizeof(lds_before)) != 0 ||
+  std::vector<int> iters;
+  for (const poisson_plan* p : b->plans) iters.push_back(p->max_iters);
+  if (b->exec && ((b->fp32 && iters != b->iters) ||
+                  std::memcmp(lds_before, b->lds, sizeof(lds_before)) != 0 ||
                   std::memcmp(items_before, b->items, sizeof(items_before)) != 0)) {
     (void)hipGraphExecDestroy(b->exec);
     (void)hipGraphDestroy(b->graph);
     b->exec = nullptr;
     b->graph = nullptr;
   }
+  b->iters = std::move(iters);
   HIP_TRY(hipMemcpy(b->djobs, host.data(), b->bytes, hipMemcpyHostToDevice));
   if (b->fp32) {
     // refinement jobs: each instance's kernels on its own block range, with
@@ -2148,7 +2154,7 @@ static int batch_upload(poisson_batch* b) {
       J.rg = r.rg;
       J.first_e = fe;
       J.first_r = fr;
-      J.max_iters = p->max_iters;
+      J.max_iters = b->iters[i];
       J.tol = p->tol;
       fe += r.nb;
       fr += r.rg.blocks;    // a multiple of 8: every job starts XCD-aligned
@@ -2222,8 +2228,9 @@ static int batch_enqueue(poisson_batch* b, hipStream_t st) {
   for (const poisson_plan* p : b->plans) {
     sweeps = std::max(sweeps, p->max_iters);
     singular = singular || p->singular;
-    single = single || (p->singular && p->max_iters == 1);
   }
+  for (int i = 0; i < n; ++i)
+    single = single || (b->plans[i]->singular && std::min(sweeps, b->iters[i]) == 1);
   const RefineJob* jobs = b->drefine;
   const dim3 blk(REFINE_NT);
   // the refinement kernels of all instances, one launch per kind (each

@@ -513,12 +513,17 @@ __device__ __forceinline__ void refine_width(const RefineJob& J, F&& f) {
   else f(std::integral_constant<int, 1>{});
 }
 
+// An instance that ran its first FP32 solve only has no update to take Phi's
+// mean from: then Phi is summed.  Read off the status block, since an
+// instance's limit and the launch's sweeps may have been set at different times.
+__device__ __forceinline__ bool refine_no_update(const double* stats) { return stats[4 + 2] < 0.0; }
+
 // the projection of f and the gauge of Phi touch singular instances only
 __global__ __launch_bounds__(REFINE_NT) void refine_batch_wsum(const RefineJob* __restrict__ jobs,
                                                                 int njobs, int init) {
   __shared__ double sh[REFINE_NT];
   const RefineJob& J = jobs[refine_job_of<false>(jobs, njobs, blockIdx.x)];
-  if (!J.singular) return;
+  if (!J.singular || (!init && !refine_no_update(J.G.stats))) return;
   const int block = blockIdx.x - J.first_e;
   if (init && block == 0) refine_init_body(J.G.stats);
   refine_width(J, [&](auto V) { refine_wsum_body<V>(J.phi, J.G, block, J.nb, sh); });
@@ -563,14 +568,13 @@ __global__ __launch_bounds__(REFINE_NT) void refine_batch_status(const RefineJob
   refine_status_body(J.G, J.nb, sweep, J.tol, sh);
 }
 
-// (an instance limited to one FP32 solve has no update to take its mean from)
 __global__ __launch_bounds__(REFINE_NT) void refine_batch_shift(const RefineJob* __restrict__ jobs,
                                                                  int njobs) {
   __shared__ double sh[REFINE_NT];
   const RefineJob& J = jobs[refine_job_of<false>(jobs, njobs, blockIdx.x)];
   if (!J.singular) return;
   refine_width(J, [&](auto V) {
-    refine_shift_body<V>(J.phi, J.G, J.max_iters == 1, blockIdx.x - J.first_e, J.nb, sh);
+    refine_shift_body<V>(J.phi, J.G, refine_no_update(J.G.stats), blockIdx.x - J.first_e, J.nb, sh);
   });
 }
 
