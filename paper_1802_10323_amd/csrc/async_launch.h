@@ -46,7 +46,7 @@ hipError_t direct_elimination_launch(const TriFastArgs<double>& a, int n, hipStr
 hipError_t direct_elimination_launch(const TriFastArgs<float>& a, int n, hipStream_t stream);
 
 // The elimination of lines of any length with a chunking (tri_line_shape in
-// tri_line.h; tri_line.hip), the geometry made for tiles of 512 / P lines, the
+// tri_line.h; tri_line.hip), the geometry made for tiles of tri_line_shape(n).nl lines, the
 // coefficient tables laid out by virtual row.  hipErrorInvalidValue if the
 // length has no chunking.
 hipError_t line_elimination_launch(const TriFastArgs<double>& a, int n, hipStream_t stream);
@@ -56,6 +56,15 @@ hipError_t line_elimination_launch(const TriFastArgs<float>& a, int n, hipStream
 // (r2r_async_wide.hip).
 hipError_t async_wide_launch(const R2RFastArgs<double>& a, int kind, int inverse,
                              hipStream_t stream);
+
+// A kernel of each unit beside poisson.hip.  A unit's code is put on the device
+// at the first use of any of its kernels; the first plan on a device looks
+// these up, so that no solve loads code (which takes device memory and, on a
+// stream being captured, may not happen at all).
+const void* async_kernel();
+const void* async_wide_kernel();
+const void* tri_async_kernel_any();
+const void* tri_line_kernel_any();
 
 // Upper bound on the blocks of the persistent launch being made on this
 // thread (0: none): the grid cap of the plan whose stage is launched.  A

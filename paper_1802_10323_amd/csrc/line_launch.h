@@ -2,8 +2,7 @@
 //
 // 56 lengths x 2 types x 3 pipelines x 2 layouts are compiled as separate
 // objects of one source (r2r_line_part.hip with POISSON_LINE_PART_INDEX = 0
-// .. 7),
-// so that the build uses every core.
+// .. 7), so that the build uses every core.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -65,6 +64,15 @@ constexpr LineShape line_shape(int bytes, int m, int layout) {
   hipError_t line_launch_##M_(const R2RFastArgs<float>& a, hipStream_t stream);
 POISSON_LINE_LENGTHS(POISSON_LINE_DECLARE)
 #undef POISSON_LINE_DECLARE
+
+// A kernel of part I (see async_kernel).
+template <int I>
+const void* line_part_kernel();
+#define POISSON_LINE_PART_DECLARE(I_) template <> const void* line_part_kernel<I_>();
+POISSON_LINE_PART_DECLARE(0) POISSON_LINE_PART_DECLARE(1) POISSON_LINE_PART_DECLARE(2)
+POISSON_LINE_PART_DECLARE(3) POISSON_LINE_PART_DECLARE(4) POISSON_LINE_PART_DECLARE(5)
+POISSON_LINE_PART_DECLARE(6) POISSON_LINE_PART_DECLARE(7)
+#undef POISSON_LINE_PART_DECLARE
 
 constexpr bool line_length(int m) {
   switch (m) {

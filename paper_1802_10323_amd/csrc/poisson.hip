@@ -363,6 +363,24 @@ static int lds_setup_once() {
   return status;
 }
 
+// The code of every unit on the current device, once per device.
+static int load_kernels_once(int dev) {
+  static std::mutex mu;
+  static std::vector<int> loaded;
+  std::lock_guard<std::mutex> lk(mu);
+  if (std::find(loaded.begin(), loaded.end(), dev) != loaded.end()) return POISSON_OK;
+  for (const void* k :
+       {async_kernel(), async_wide_kernel(), tri_async_kernel_any(), tri_line_kernel_any(),
+        line_part_kernel<0>(), line_part_kernel<1>(), line_part_kernel<2>(), line_part_kernel<3>(),
+        line_part_kernel<4>(), line_part_kernel<5>(), line_part_kernel<6>(), line_part_kernel<7>()}) {
+    hipFuncAttributes attr;
+    const hipError_t e = hipFuncGetAttributes(&attr, k);
+    if (e != hipSuccess) return fail(POISSON_EHIP, "loading kernels: %s", hipGetErrorString(e));
+  }
+  loaded.push_back(dev);
+  return POISSON_OK;
+}
+
 static int ilog2(int v) {
   int l = 0;
   while ((1 << (l + 1)) <= v) ++l;
@@ -1269,7 +1287,7 @@ extern "C" poisson_plan* plan_create_helmholtz(int nx, int ny, int nz, double dx
   }
   p->tab_bytes = host.size();
   if (hipGetDevice(&p->device) != hipSuccess) { fail(POISSON_EHIP, "hipGetDevice failed"); delete p; return nullptr; }
-  if (lds_setup_once()) { delete p; return nullptr; }
+  if (lds_setup_once() || load_kernels_once(p->device)) { delete p; return nullptr; }
   if (hipMalloc(&p->dtab, p->tab_bytes) != hipSuccess) { fail(POISSON_ENOMEM, "table allocation (%zu B) failed", p->tab_bytes); delete p; return nullptr; }
   if (hipMemcpy(p->dtab, host.data(), p->tab_bytes, hipMemcpyHostToDevice) != hipSuccess) {
     fail(POISSON_EHIP, "table upload failed");

@@ -7,6 +7,10 @@
 
 namespace poisson_dev {
 
+const void* async_wide_kernel() {
+  return reinterpret_cast<const void*>(&r2r_regstage_kernel<double, RegStageCfg, 0, 0, false>);
+}
+
 hipError_t async_wide_launch(const R2RFastArgs<double>& a, int kind, int inverse,
                              hipStream_t stream) {
   using C = FastVar<256, 0>;

@@ -8,11 +8,15 @@
 
 namespace poisson_dev {
 
+// FP64 values of a radix-20 or radix-25 butterfly take more than 128 registers
+template <typename T, int M, int LAYOUT>
+using LineTile = LineCfg<M, line_shape(sizeof(T), M, LAYOUT).nl, line_shape(sizeof(T), M, LAYOUT).nt,
+                         sizeof(T) == 8 && line_shape(sizeof(T), M, LAYOUT).waves == 4 ? 18 : 25>;
+
 template <typename T, int M, int LAYOUT>
 static hipError_t line_launch_layout(const R2RFastArgs<T>& a, hipStream_t stream) {
   constexpr LineShape S = line_shape(sizeof(T), M, LAYOUT);
-  // FP64 values of a radix-20 or radix-25 butterfly take more than 128 registers
-  using C = LineCfg<M, S.nl, S.nt, sizeof(T) == 8 && S.waves == 4 ? 18 : 25>;
+  using C = LineTile<T, M, LAYOUT>;
   void (*k)(R2RFastArgs<T>) = a.kind >= K_ND ? r2r_line_kernel<T, C, PIPE_IV, LAYOUT, S.waves>
                               : a.inverse    ? r2r_line_kernel<T, C, PIPE_INV, LAYOUT, S.waves>
                                              : r2r_line_kernel<T, C, PIPE_FWD, LAYOUT, S.waves>;
@@ -37,5 +41,14 @@ static hipError_t line_launch(const R2RFastArgs<T>& a, hipStream_t stream) {
 #define POISSON_CAT2(a, b) a##b
 #define POISSON_CAT(a, b) POISSON_CAT2(a, b)
 POISSON_CAT(POISSON_LINE_PART, POISSON_LINE_PART_INDEX)(POISSON_LINE_DEFINE)
+
+#define POISSON_LINE_M(M_) M_,
+template <>
+const void* line_part_kernel<POISSON_LINE_PART_INDEX>() {
+  constexpr int m[] = {POISSON_CAT(POISSON_LINE_PART, POISSON_LINE_PART_INDEX)(POISSON_LINE_M)};
+  constexpr int M = m[0];
+  return reinterpret_cast<const void*>(
+      &r2r_line_kernel<double, LineTile<double, M, 0>, PIPE_FWD, 0, line_shape(8, M, 0).waves>);
+}
 
 }  // namespace poisson_dev

@@ -63,6 +63,8 @@ hipError_t launch_direct_n(const TriFastArgs<T>& a, int n, hipStream_t st) {
 
 }  // namespace
 
+const void* tri_async_kernel_any() { return reinterpret_cast<const void*>(&tri_async_kernel<double, 4, 16, 0>); }
+
 hipError_t direct_elimination_launch(const TriFastArgs<double>& a, int n, hipStream_t stream) {
   return launch_direct_n<double>(a, n, stream);
 }

@@ -18,7 +18,8 @@ hipError_t launch(const TriFastArgs<T>& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// f(rpc, p, nl) for the chunking of every length, each once
+// The launch of n's chunking, among those of the lengths from N on (one for
+// each number of virtual rows)
 template <typename T, int N>
 hipError_t launch_n(const TriFastArgs<T>& a, int n, hipStream_t st) {
   if constexpr (N > 512) {
@@ -32,6 +33,11 @@ hipError_t launch_n(const TriFastArgs<T>& a, int n, hipStream_t st) {
 }
 
 }  // namespace
+
+const void* tri_line_kernel_any() {
+  constexpr TriLineShape S = tri_line_shape(17);
+  return reinterpret_cast<const void*>(&tri_line_kernel<double, S.rpc, S.p, S.nl, S.waves, 0>);
+}
 
 hipError_t line_elimination_launch(const TriFastArgs<double>& a, int n, hipStream_t stream) {
   return launch_n<double, 17>(a, n, stream);
