@@ -166,8 +166,13 @@ int solve_status(poisson_plan* plan, int* iters, double* last_update_rel);
  * (DEVICE pointers), on `stream`.  An FP32 + refinement plan may appear only
  * once (its workspace is per plan; POISSON_EINVAL otherwise).  Same result
  * per instance as solve() with the same kernel variants, bit for bit
- * (batched launches use transform variants 0-3; against solve() with the
- * staging transforms, variants 4-6, results agree to rounding).  When every
+ * (batched launches use transform variants 0-3 and elimination variants 0-1).
+ * Where solve() runs other kernels, as it does by default (see the autotuner),
+ * the two agree to rounding: against the staging transforms to 1e-15, against
+ * a length's own kernels to the error of the batch's elimination, whose
+ * pivots are the less exact (28 FP64 problems of 64 to 256 points an axis:
+ * batches 8e-15 to 9e-13 from the exact solution, single solves 2e-15 to
+ * 2e-13, up to 9.5e-13 from each other).  When every
  * plan's lengths have size-specialised kernels (batch_create) and all plans
  * have one precision mode, the solves run as batched launches (see below)
  * and the call waits for `stream` to complete (it frees its temporary job
@@ -277,8 +282,22 @@ int plan_autotune(poisson_plan* plan, double* scratch, int reps, hipStream_t str
  * line length n, layout 0 (strided) or 1 (contiguous), fp64 1 or 0. */
 int tuned_variant(int family, int n, int layout, int fp64);
 
-/* Set that entry by hand (POISSON_EUNSUPPORTED if n has no variants). */
+/* Set that entry by hand (POISSON_EUNSUPPORTED if n has no variants): solves
+ * then run this variant, and no longer the length's own kernels.  Writing
+ * tuned_variant() back therefore does not restore an entry; the pair below
+ * does. */
 int set_tuned_variant(int family, int n, int layout, int fp64, int variant);
+
+/* The entry as it stands, to be written back later: POISSON_UNSET (nothing
+ * tuned or set: the defaults above), a variant, or a variant +
+ * POISSON_LINE_FASTER (solves run the length's own kernels, batches that
+ * variant).  Same errors as set_tuned_variant (and POISSON_EUNSUPPORTED for
+ * POISSON_LINE_FASTER on transforms of length 512, which have no kernels of
+ * their own). */
+#define POISSON_UNSET (-1)
+#define POISSON_LINE_FASTER 256
+int tuned_entry(int family, int n, int layout, int fp64, int* entry);
+int set_tuned_entry(int family, int n, int layout, int fp64, int entry);
 
 /* ---- continuous-batching server (many independent solves, Sec. 2.1 each) ----
  *

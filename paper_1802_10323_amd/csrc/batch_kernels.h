@@ -8,8 +8,10 @@
 // blocks of the persistent grid take contiguous runs of items (one run per
 // XCD, interleaved over that XCD's blocks), find the job of each item by a
 // binary search over the jobs' first items (block-uniform, scalar loads),
-// and run the same tile function as the single-instance kernel, so a
-// batched solve is bitwise identical to solving the instances one by one.
+// and run the same tile function as the single-instance kernel of the same
+// variant, so a batched solve is bitwise identical to solving the instances
+// one by one in these variants (by default single solves run the per-length
+// kernels instead, r2r_line.h and tri_line.h, which round differently).
 //
 // LDS tables that depend on the job (transform twiddles: on the length and
 // the type class; elimination coefficients: on the instance) are reloaded

@@ -292,10 +292,10 @@ static int default_choice(int family, int bytes, int n, int layout) {
 // Per-length form (r2r_line.h, tri_line.h) in the variant table: used where
 // nothing was tuned or set, and where the autotuner found it faster than every
 // variant (the table then holds the fastest variant with kLineFaster added).
-static constexpr int kLineFaster = 256;
+static constexpr int kLineFaster = POISSON_LINE_FASTER;
 
 // The entry as it stands, or -1.
-static int tuned_entry(int family, int bytes, int n, int layout) {
+static int table_entry(int family, int bytes, int n, int layout) {
   int dev = 0;
   (void)hipGetDevice(&dev);
   std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -304,15 +304,18 @@ static int tuned_entry(int family, int bytes, int n, int layout) {
 }
 
 static int tuned_choice(int family, int bytes, int n, int layout) {
-  const int e = tuned_entry(family, bytes, n, layout);
+  const int e = table_entry(family, bytes, n, layout);
   return e < 0 ? default_choice(family, bytes, n, layout) : e & (kLineFaster - 1);
 }
 
+// v < 0: nothing tuned or set.
 static void set_tuned_choice(int family, int bytes, int n, int layout, int v) {
   int dev = 0;
   (void)hipGetDevice(&dev);
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  g_tune[std::make_tuple(dev, family, bytes, n, layout)] = v;
+  const auto key = std::make_tuple(dev, family, bytes, n, layout);
+  if (v < 0) g_tune.erase(key);
+  else g_tune[key] = v;
 }
 
 static int lds_setup_once() {
@@ -606,7 +609,7 @@ template <typename T>
 static bool line_applies(const AxisTables& A) {
   if (!line_length(A.m)) return false;
   if (with_fast_cfg(A.m, 0, [](auto) { return 0LL; }) != 0) return true;
-  const int e = tuned_entry(0, sizeof(T), A.m, A.axis == 0);
+  const int e = table_entry(0, sizeof(T), A.m, A.axis == 0);
   return e < 0 || (e & kLineFaster) != 0;
 }
 
@@ -747,7 +750,7 @@ static bool tri_line_applies(const poisson_plan* p) {
   const int n = p->dims[p->s];
   if (!p->line_rows || (p->plane_mats && (n == 32 || n == 48))) return false;
   if (!tri_fast_length(n)) return true;
-  const int e = tuned_entry(1, sizeof(T), n, p->s == 0);
+  const int e = table_entry(1, sizeof(T), n, p->s == 0);
   return e < 0 ? p->s != 0 : (e & kLineFaster) != 0;
 }
 
@@ -2465,14 +2468,40 @@ extern "C" int batch_autotune(poisson_batch* b, int reps, hipStream_t st, double
   return batch_upload(b);
 }
 
+static int check_table_length(int family, int n) {
+  const bool ok = family == 0 ? (n % 2 == 0 && with_fast_cfg(n / 2, 0, [](auto) { return 0LL; }) == 0)
+                              : tri_fast_length(n);
+  return ok ? POISSON_OK : fail(POISSON_EUNSUPPORTED, "length %d has no size-specialised kernels", n);
+}
+
 extern "C" int set_tuned_variant(int family, int n, int layout, int fp64, int variant) {
   if (family != 0 && family != 1) return fail(POISSON_EINVAL, "family must be 0 or 1");
   const int count = family == 0 ? kFastVariants : kTriVariants;
   if (variant < 0 || variant >= count) return fail(POISSON_EINVAL, "variant must be in [0, %d)", count);
-  const bool ok = family == 0 ? (n % 2 == 0 && with_fast_cfg(n / 2, 0, [](auto) { return 0LL; }) == 0)
-                              : tri_fast_length(n);
-  if (!ok) return fail(POISSON_EUNSUPPORTED, "length %d has no size-specialised kernels", n);
+  if (int rc = check_table_length(family, n)) return rc;
   set_tuned_choice(family, fp64 ? 8 : 4, family == 0 ? n / 2 : n, layout ? 1 : 0, variant);
+  return POISSON_OK;
+}
+
+extern "C" int tuned_entry(int family, int n, int layout, int fp64, int* entry) {
+  if (family != 0 && family != 1) return fail(POISSON_EINVAL, "family must be 0 or 1");
+  if (!entry) return fail(POISSON_EINVAL, "null argument");
+  if (int rc = check_table_length(family, n)) return rc;
+  *entry = table_entry(family, fp64 ? 8 : 4, family == 0 ? n / 2 : n, layout ? 1 : 0);
+  return POISSON_OK;
+}
+
+extern "C" int set_tuned_entry(int family, int n, int layout, int fp64, int entry) {
+  if (family != 0 && family != 1) return fail(POISSON_EINVAL, "family must be 0 or 1");
+  const int count = family == 0 ? kFastVariants : kTriVariants;
+  const bool line = entry >= kLineFaster;
+  const int variant = line ? entry - kLineFaster : entry;
+  if (variant < POISSON_UNSET || variant >= count)
+    return fail(POISSON_EINVAL, "entry must be unset or a variant in [0, %d), with or without %d", count, kLineFaster);
+  if (int rc = check_table_length(family, n)) return rc;
+  if (line && family == 0 && !line_length(n / 2))
+    return fail(POISSON_EUNSUPPORTED, "length %d has no per-length transform", n);
+  set_tuned_choice(family, fp64 ? 8 : 4, family == 0 ? n / 2 : n, layout ? 1 : 0, entry);
   return POISSON_OK;
 }
 

@@ -48,6 +48,10 @@ SIGNATURES = {
     "batch_autotune": (ctypes.c_int, [_VP, ctypes.c_int, _VP, ctypes.POINTER(ctypes.c_double)]),
     "plan_autotune": (ctypes.c_int, [_VP, _VP, ctypes.c_int, _VP, ctypes.POINTER(ctypes.c_double)]),
     "tuned_variant": (ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int]),
+    "tuned_entry": (ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int,
+                                   ctypes.POINTER(ctypes.c_int)]),
+    "set_tuned_entry": (ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int,
+                                       ctypes.c_int]),
     "set_tuned_variant": (ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int,
                                          ctypes.c_int]),
     "server_create": (_VP, [ctypes.c_int, ctypes.c_size_t, ctypes.c_int]),
@@ -492,3 +496,19 @@ def tuned_variant(family, n, layout, fp64=True):
 
 def set_tuned_variant(family, n, layout, variant, fp64=True):
     _check(lib().set_tuned_variant(int(family), int(n), int(layout), int(bool(fp64)), int(variant)))
+
+
+UNSET = -1            # tuned_entry: nothing tuned or set
+LINE_FASTER = 256     # tuned_entry: added to the variant where solves run the length's own kernels
+
+
+def tuned_entry(family, n, layout, fp64=True):
+    """The table entry as it stands, for ``set_tuned_entry`` to write back:
+    UNSET, a variant, or a variant + LINE_FASTER."""
+    entry = ctypes.c_int()
+    _check(lib().tuned_entry(int(family), int(n), int(layout), int(bool(fp64)), ctypes.byref(entry)))
+    return entry.value
+
+
+def set_tuned_entry(family, n, layout, entry, fp64=True):
+    _check(lib().set_tuned_entry(int(family), int(n), int(layout), int(bool(fp64)), int(entry)))
