@@ -263,11 +263,10 @@ int batch_autotune(poisson_batch* batch, int reps, hipStream_t stream, double* r
  * length 512, strided eliminations) while their entry is neither set by hand
  * nor tuned.  The autotuner times them too, and solves keep them where they
  * beat every variant; the entry then still names the fastest variant.
- * pressure_correction always runs the variants and the size-generic kernels
- * for its transforms and eliminations: its Phi on an already divergence-free
- * velocity is the solve of rounding noise, which any other rounding changes.
- * Plans and batches read the table when they launch (batches when they are bound; batches use the
- * synchronous variants only: transforms 0-3, elimination 0-1). */
+ * pressure_correction on an FP64 plan runs the variants and the size-generic
+ * kernels always (see there).  Plans and batches read the table when they
+ * launch (batches when they are bound; batches use the synchronous variants
+ * only: transforms 0-3, elimination 0-1). */
 
 /* Time every variant of this plan's kernels (both transformed axes and the
  * elimination, FP64 and FP32) on `scratch` (DEVICE, at least nx*ny*nz
@@ -400,8 +399,15 @@ int projection_update(poisson_plan* plan, const double* phi, double gamma_dt, do
                       double* v, double* w, double* p, hipStream_t stream);
 
 /* The whole step on `stream`: projection_rhs into phi (caller-owned, DEVICE,
- * nx*ny*nz doubles), solve(plan, phi) in the plan's precision mode, then
- * projection_update.  On return phi holds the correction pressure. */
+ * nx*ny*nz doubles), the solve in the plan's precision mode, then
+ * projection_update.  On return phi holds the correction pressure.
+ * On a refined plan the solve is solve(plan, phi).  On an FP64 plan it is
+ * solve() in the kernels of the variant table and the size-generic ones only,
+ * the same phi to rounding: on a velocity that is divergence-free already,
+ * phi is the solve of rounding noise, and these keep it what it was in
+ * earlier versions.  They are slower where a length has no variants (270 x
+ * 150 x 162: 282 against 115 us a solve); a caller who has no use for the phi
+ * of such a call makes the three calls instead. */
 int pressure_correction(poisson_plan* plan, double* u, double* v, double* w, double* p,
                         double gamma_dt, double* phi, hipStream_t stream);
 

@@ -613,13 +613,17 @@ static bool line_applies(const AxisTables& A) {
   return e < 0 || (e & kLineFaster) != 0;
 }
 
-// Kernels that a solve may use.  pressure_correction takes kSteady: applied
-// to a velocity that is divergence-free already, its right-hand side is the
-// rounding noise of the divergence, and phi the solve of that noise, so that
-// any other order of operations gives another phi altogether.  There the
-// kernels stay those whose bits callers have seen: the variants and the
-// size-generic ones (270 x 150 x 162: 282 us a solve against 121 with the
-// per-length kernels).
+// Kernels that an FP64 solve may use.  pressure_correction takes kSteady: the
+// variants of the table and the size-generic kernels, which it ran before the
+// per-length ones were there.  Applied a second time to the same velocity, its
+// right-hand side is the rounding noise of a divergence that is zero, and phi
+// the solve of that noise (128 x 64 x 48: 8e-17 after 5e-2); with any other
+// rounding anywhere in the solve it is another field (off by 0.5 to 1.2 of its
+// norm, while u, v, w and p agree to 1e-15).  The steady kernels keep that phi
+// what it was, at a price: 282 us a solve against 115 at 270 x 150 x 162; 308
+// us a whole correction against 295 at 512 x 128 x 128.  projection_rhs, solve
+// and projection_update called one by one have the fast solve.  A refined plan's correction runs
+// solve(): what is left of it is within the tolerance, not of fixed bits.
 enum Route { kFastest, kSteady };
 
 // out64 (FP32 only): write the widened result there instead of in place.
@@ -848,11 +852,12 @@ static int launch_tridiag(const poisson_plan* p, T* data, hipStream_t st,
                           const double* skip = nullptr, Route route = kFastest) {
   t_grid_cap = p->grid_cap;
   if (route == kFastest && tri_line_applies<T>(p)) return launch_tri_line<T>(p, data, st, skip);
-  if (p->pad_n) {   // padded lines: the plain chunked kernel of length pad_n
-    return (int)with_tri_cfg(p->pad_n, 0, [&](auto cfg) {
-      using C = decltype(cfg);
-      return (long long)launch_tri_fast<T, C::RPC, C::P>(p, data, st, skip);
-    });
+  if constexpr (sizeof(T) == 8) {   // steady route, padded lines: the plain chunked kernel of length pad_n
+    if (p->pad_n)
+      return (int)with_tri_cfg(p->pad_n, 0, [&](auto cfg) {
+        using C = decltype(cfg);
+        return (long long)launch_tri_fast<T, C::RPC, C::P>(p, data, st, skip);
+      });
   }
   if (!p->generic_tri) {
     const int n = p->dims[p->s];
@@ -1390,12 +1395,12 @@ extern "C" int plan_set_precision(poisson_plan* p, int mode, double tol, int max
   return POISSON_OK;
 }
 
-static int solve_refined(poisson_plan* p, double* rhs, hipStream_t st, Route route);
+static int solve_refined(poisson_plan* p, double* rhs, hipStream_t st);
 
 static int solve_route(poisson_plan* p, double* rhs, hipStream_t st, Route route) {
   if (!p || !rhs) return fail(POISSON_EINVAL, "null argument");
   if (int rc = misaligned(rhs, "rhs")) return rc;
-  if (p->mode == POISSON_FP32_REFINED) return solve_refined(p, rhs, st, route);
+  if (p->mode == POISSON_FP32_REFINED) return solve_refined(p, rhs, st);
   p->last_iters = 1;
   p->last_rel = 0.0;
   p->last_converged = 1;
@@ -1558,24 +1563,23 @@ static int refine_end(const poisson_plan* p, const RefineWork& W, double* rhs, h
 }
 
 // The whole refined solve on workspace W.
-static int run_refined(const poisson_plan* p, const RefineWork& W, double* rhs, hipStream_t st,
-                       Route route = kFastest) {
+static int run_refined(const poisson_plan* p, const RefineWork& W, double* rhs, hipStream_t st) {
   int rc;
   if ((rc = refine_begin(p, W, rhs, st))) return rc;
   // the first FP32 solve's last pass writes Phi (widened) into rhs
-  if ((rc = solve_typed<float>(p, W.e32, st, nullptr, rhs, route))) return rc;
+  if ((rc = solve_typed<float>(p, W.e32, st, nullptr, rhs))) return rc;
   for (int sweep = 1; sweep < W.max_iters; ++sweep) {
     if ((rc = refine_sweep_begin(p, W, rhs, st))) return rc;
-    if ((rc = solve_typed<float>(p, W.e32, st, W.stats, nullptr, route))) return rc;
+    if ((rc = solve_typed<float>(p, W.e32, st, W.stats))) return rc;
     if ((rc = refine_sweep_end(p, W, rhs, sweep, st))) return rc;
   }
   return refine_end(p, W, rhs, st);
 }
 
 // The plan's refined solve, and the status copy for solve_status.
-static int solve_refined(poisson_plan* p, double* rhs, hipStream_t st, Route route) {
+static int solve_refined(poisson_plan* p, double* rhs, hipStream_t st) {
   const RefineWork W = plan_work(p);
-  const int rc = run_refined(p, W, rhs, st, route);
+  const int rc = run_refined(p, W, rhs, st);
   if (rc) return rc;
   HIP_TRY(hipMemcpyAsync(p->stats_host, p->stats, REFINE_PARTIALS * sizeof(double),
                          hipMemcpyDeviceToHost, st));
