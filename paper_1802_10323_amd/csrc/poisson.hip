@@ -603,8 +603,10 @@ static int launch_line(const poisson_plan* p, const AxisTables& A, int inverse, 
 // tile holds less than a wave's work): every length without variants, and the
 // others where no variant was set or tuned to be faster (length 512 has the
 // staging forms only).  Gains over the variants on fields of 2^25 points, along
-// x / y: n = 128 4.6 / 4.9 -> 5.8 / 5.3 TB/s, 192 4.9 / 5.1 -> 6.4 / 6.1, 256
-// 5.6 / 5.4 -> 6.1 / 5.8, 288 3.5 / 3.6 -> 5.8 / 5.7.
+// x / y: n = 128 4.6 / 4.9 -> 6.3 / 6.2 TB/s, 192 4.9 / 5.1 -> 6.3 / 5.8, 256
+// 5.6 / 5.4 -> 6.3 / 5.9, 288 3.5 / 3.6 -> 5.4 / 5.7.  Whole solves, both
+// transforms in variants -> per length: 64^3 40 -> 25.7 us, 96^3 46 -> 38, 128^3
+// 64 -> 60, 192^3 132 -> 110.
 template <typename T>
 static bool line_applies(const AxisTables& A) {
   if (!line_length(A.m)) return false;
@@ -748,7 +750,9 @@ static int launch_tri_line(const poisson_plan* p, T* data, hipStream_t st, const
 // 32 and 48 points of a small grid their 16-lane chunks (more lanes at work on
 // so few lines).  Measured on 512 x ny x n fields of 2^25 points, singular:
 // n = 100 1.38 -> 5.2 TB/s, 144 1.77 -> 5.9, 250 2.19 -> 5.9, 400 1.87 -> 4.4;
-// regular: 191 (padded before) 4.50 -> 5.9.
+// regular: 191 (padded before) 4.50 -> 5.9.  Whole solves with strided lines
+// of a specialised length, its variant -> this: 128^3 61 -> 60 us, 256^3 239 ->
+// 227, refined 256^3 613 -> 578, 384^3 988 -> 993, 192^3 108 -> 110.
 template <typename T>
 static bool tri_line_applies(const poisson_plan* p) {
   const int n = p->dims[p->s];

@@ -106,15 +106,16 @@ __global__ __launch_bounds__(PROJ_NT) void proj_rhs_kernel(const double* __restr
 // gradient reads no other plane (the x and y neighbours come from the
 // lines the adjacent lanes and rows load).  The face values and p, each
 // read and written by one thread only, take the nontemporal hint; Phi,
-// which the neighbouring lanes read again, does not.  No lane skips a
-// load or a store on account of its place in the grid: at a wall the
-// neighbour's address is the cell's own and the gradient is selected, and
-// the high wall faces are behind uniform branches, so a plane's waits leave
-// the next plane's reads and the stores in flight.  Bound by HBM.  Measured,
-// branches per lane -> selects: 114 -> 92 us on 512 x 128 x 128 (P, NN, NN;
-// 6.5 TB/s), 329 -> 307 us on 512 x 256 x 192 (P, P, NN; 5.9 TB/s), 128 ->
-// 101 us on 270 x 150 x 162 (NN, P, ND), 1.63 -> 1.60 ms on the periodic
-// 512^3 (6.0 TB/s; out of place, at the end of a time step, 1.82 -> 1.85).
+// which the neighbouring lanes read again, does not.  At a wall the
+// neighbour's address is the cell's own and the gradient is selected, and the
+// high wall faces are read behind uniform branches, so that no lane skips a
+// load; only the last column's store of its high wall face is its own.  A
+// plane's waits then leave the next plane's reads and the stores in flight.
+// Bound by HBM.  Measured, branches per lane -> selects: 114 -> 92 us on 512 x
+// 128 x 128 (P, NN, NN; 6.5 TB/s), 329 -> 307 us on 512 x 256 x 192 (P, P, NN;
+// 5.9 TB/s), 128 -> 101 us on 270 x 150 x 162 (NN, P, ND; 97 with the shorter z
+// ranges of proj_tiles), 1.63 -> 1.60 ms on the periodic 512^3 (6.0 TB/s; out
+// of place, at the end of a time step, 1.82 -> 1.83).
 __global__ __launch_bounds__(PROJ_NT) void proj_update_zmarch_kernel(
     const double* __restrict__ phi, double gdt, const double* u_in, const double* v_in,
     const double* w_in, double* u, double* v, double* w, double* __restrict__ p, ProjGeom G) {

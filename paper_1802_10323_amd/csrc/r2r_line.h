@@ -12,21 +12,25 @@
 //    pre-twiddle as the first pass reads its inputs, the forward split and
 //    the DCT-IV post-twiddle as the tile is stored.  The FFT passes are the
 //    only other LDS round trips, two of them up to M = 256 and three beyond;
-//  * no load and no store sits behind a branch: lanes past the end of a line
-//    and lines past the end of the field repeat a valid one (the same value
-//    to the same address), so the compiler can count the memory operations
-//    in flight and its waits for the next tile's loads leave the current
-//    tile's stores in flight;
+//  * no lane skips a load or a store: lanes past the end of a line and lines
+//    past the end of the field repeat a valid one (the same value to the same
+//    address), so the compiler can count the memory operations in flight and
+//    its waits for the next tile's loads leave the current tile's stores in
+//    flight (the one branch around stores, in the contiguous forward DFT,
+//    takes pairs of points on one side and the single ones of k = 0 on the
+//    other);
 //  * the twiddles live in LDS.
 //
 // Bound: HBM, like every stage (16 B per point in FP64).  The size-generic
 // kernel ran at 1.7-2.4 TB/s (64-bit address arithmetic and run-time
 // divisions in every element, each stage a call that drains the loads and
 // stores in flight); this one on fields of 2^25 points, the types and both
-// directions averaged, along x / y: n = 192 6.4 / 6.1 TB/s, 250 5.6 / 4.9
-// (generic 2.2), 288 5.8 / 5.7, 480 6.0 / 5.9 (2.3), 640 5.2 / 4.7 (1.9), 1024
-// 4.7 / 4.4 (2.4; its tile leaves room for one block to a CU).  Whole solves: 270
-// x 150 x 162 281 -> 114 us, 1024 x 640 x 320 8.16 -> 3.77 ms.
+// directions averaged, along x / y: n = 192 6.3 / 5.8 TB/s, 250 5.9 / 5.6
+// (generic 2.2), 288 5.4 / 5.7, 480 6.0 / 5.8 (2.3), 640 5.0 / 4.8 (1.9), 1024
+// 4.7 / 4.4 (2.4; its tile leaves room for one block to a CU); on the larger
+// field of a 1024 x 640 x 320 solve 640 along y runs at 4.2.  Another
+// placement of the field moves a figure by up to 10 %.  Whole solves: 270
+// x 150 x 162 281 -> 115 us, 1024 x 640 x 320 8.16 -> 3.80 ms.
 //
 // Three pipelines: PIPE_FWD (real DFT, DCT-II, DST-II), PIPE_INV (their
 // inverses), PIPE_IV (DCT-IV, DST-IV, both directions).  Two layouts: strided

@@ -20,7 +20,7 @@
 // it already: the gauge's mean of Phi comes from the last update.  Measured
 // on the 512 x 256 x 192 channel (singular), before -> after: mean of f 56 -> 31
 // us, copy and cast 94 -> 85, residual 154 -> 112, update 84 -> 76, gauge 114 ->
-// 57, four launches fewer; the refined solve 992 -> 842 us.
+// 57, four launches fewer; the refined solve 992 -> 844 us.
 #pragma once
 #include <algorithm>
 #include <type_traits>

@@ -1,5 +1,6 @@
 // tri_line.h - elimination of the reduced systems of Eq. (poi_reduced) for
-// lines of any length 17 <= n <= 512: n = RPC P - m rows in P chunks, the
+// lines of any length 17 <= n <= 512 (also those with variants, where the lines
+// are strided and nothing was tuned or set): n = RPC P - m rows in P chunks, the
 // first m < P chunks one row shorter than the others.
 //
 // The same chunked elimination as tri_fast.h (tri_line_solve), with a short
